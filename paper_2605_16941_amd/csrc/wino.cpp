@@ -232,18 +232,20 @@ double norm_bytes(int M, int d, const Pending& p) {
 // only on each sequence's current-block and shadow rows (the only rows the
 // decision reads; keys and values still come from every row), gathered into
 // xc = [B * (Lb + Ls), d]; the caller then reads the final rows from xc.
+// x: the residual stream's buffer [B * T, d], 16-byte aligned (null: the workspace's).
 wino_status run_forward(wino_ctx* c, const StepGeom& g, const int32_t* tokens, int n_sub,
-                        hipStream_t st, bool compact = false) {
+                        hipStream_t st, bool compact = false, float* x = nullptr) {
   const wino_model_config& m = c->cfg;
   const int d = m.d_model, F = m.d_ff, H = m.n_heads, hd = m.head_dim;
   const int M = g.B * g.T;
   compact = compact && n_sub >= 2 * m.n_layers;
   Pending pend;  // split-K partials not yet added to x
-  float* xr = c->x();  // residual stream of the rows being computed
+  if (!x) x = c->x();
+  float* xr = x;  // residual stream of the rows being computed
   int Mr = M;
   {
     Bracket br(c, K_EMBED_NORM, st);
-    launch_embed_norm(g, tokens, c->tok_emb, m.vocab, c->attn_norm[0], m.rms_eps, d, c->x(), c->h(), st);
+    launch_embed_norm(g, tokens, c->tok_emb, m.vocab, c->attn_norm[0], m.rms_eps, d, x, c->h(), st);
     HIP_TRY(c, hipGetLastError());
     br.done(0, (double)M * d * (2 + 4 + 2));
   }
@@ -270,7 +272,7 @@ wino_status run_forward(wino_ctx* c, const StepGeom& g, const int32_t* tokens, i
     }
     if (last_compact) {
       Bracket br(c, K_RMSNORM, st);
-      launch_gather_block_rows(g, c->x(), d, c->xc(), st);
+      launch_gather_block_rows(g, x, d, c->xc(), st);
       HIP_TRY(c, hipGetLastError());
       xr = c->xc();
       Mr = g.B * (g.Lb + g.Ls);
@@ -281,7 +283,7 @@ wino_status run_forward(wino_ctx* c, const StepGeom& g, const int32_t* tokens, i
     oc.A = c->att(); oc.lda = d; oc.W = c->w_o[l]; oc.ldw = d;
     oc.M = Mr; oc.N = d; oc.K = d; oc.epi = EPI_RESIDUAL; oc.outf = xr; oc.ldc = d;
     {
-      Bracket br(c, xr == c->x() ? K_GEMM_O : K_GEMM_LAST, st);
+      Bracket br(c, xr == x ? K_GEMM_O : K_GEMM_LAST, st);
       hipError_t e;
       pend = residual_gemm(c, oc, st, &e);
       HIP_TRY(c, e);
@@ -301,7 +303,7 @@ wino_status run_forward(wino_ctx* c, const StepGeom& g, const int32_t* tokens, i
     gc.A = c->h(); gc.lda = d; gc.W = c->w_gu[l]; gc.ldw = d;
     gc.M = Mr; gc.N = 2 * F; gc.K = d; gc.epi = EPI_SWIGLU; gc.outh = c->u(); gc.ldc = F; gc.F = F;
     {
-      Bracket br(c, xr == c->x() ? K_GEMM_GATEUP : K_GEMM_LAST, st);
+      Bracket br(c, xr == x ? K_GEMM_GATEUP : K_GEMM_LAST, st);
       HIP_TRY(c, launch_gemm(gc, st));
       br.done(2.0 * Mr * 2.0 * F * d, 2.0 * ((double)Mr * d + 2.0 * F * d + (double)Mr * F));
     }
@@ -310,7 +312,7 @@ wino_status run_forward(wino_ctx* c, const StepGeom& g, const int32_t* tokens, i
     dc.A = c->u(); dc.lda = F; dc.W = c->w_down[l]; dc.ldw = F;
     dc.M = Mr; dc.N = d; dc.K = F; dc.epi = EPI_RESIDUAL; dc.outf = xr; dc.ldc = d;
     {
-      Bracket br(c, xr == c->x() ? K_GEMM_DOWN : K_GEMM_LAST, st);
+      Bracket br(c, xr == x ? K_GEMM_DOWN : K_GEMM_LAST, st);
       hipError_t e;
       pend = residual_gemm(c, dc, st, &e);
       HIP_TRY(c, e);
@@ -318,7 +320,7 @@ wino_status run_forward(wino_ctx* c, const StepGeom& g, const int32_t* tokens, i
     }
     if (l + 1 < m.n_layers && 2 * (l + 1) < n_sub) {
       Bracket br(c, K_RMSNORM, st);
-      launch_rmsnorm(c->x(), c->attn_norm[l + 1], m.rms_eps, M, d, c->h(), c->part(), pend.n,
+      launch_rmsnorm(x, c->attn_norm[l + 1], m.rms_eps, M, d, c->h(), c->part(), pend.n,
                      pend.row0, st, c->f16);
       HIP_TRY(c, hipGetLastError());
       br.done(0, norm_bytes(M, d, pend));
@@ -859,8 +861,11 @@ wino_status wino_debug_forward(wino_ctx* c, const wino_params* p, const int32_t*
   if (n_sublayers < 0 || n_sublayers > 2 * c->cfg.n_layers) return WINO_ERR_INVALID_ARG;
   hipStream_t st = static_cast<hipStream_t>(stream);
   const StepGeom g = make_geom(c, p, d_block_start);
-  s = run_forward(c, g, d_tokens, n_sublayers, st);
-  if (s != WINO_OK) return s;
+  // the stream accumulates in the caller's buffer where the kernels' 16-byte
+  // accesses allow it; otherwise in the workspace, copied out at the end
+  const bool direct = reinterpret_cast<uintptr_t>(d_out) % 16 == 0;
+  s = run_forward(c, g, d_tokens, n_sublayers, st, false, direct ? d_out : nullptr);
+  if (s != WINO_OK || direct) return s;
   HIP_TRY(c, hipMemcpyAsync(d_out, c->x(), sizeof(float) * (size_t)g.B * g.T * c->cfg.d_model,
                             hipMemcpyDeviceToDevice, st));
   return WINO_OK;
