@@ -165,6 +165,11 @@ __device__ __forceinline__ float sum_xor32(float x) {
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
+__device__ __forceinline__ int min_xor32(int x) {
+  const auto r = __builtin_amdgcn_permlane32_swap((uint32_t)x, (uint32_t)x, false, false);
+  return min((int)r[0], (int)r[1]);
+}
+
 // LDS-DMA of 16 bytes per lane (global_load_lds_dwordx4) into the 1 KB block
 // at l + j KB (j = 0..3): the LDS base goes to M0 and j KB into the
 // instruction's offset, which applies to the global address as well, so g

@@ -447,10 +447,16 @@ __device__ __forceinline__ void epi_qkv_rope(const GemmCall& c, f32x16 (&acc)[FM
   }
 }
 
-// LM head epilogue: per row of the tile, statistics over the BN columns.
+// LM head epilogue: per row of the tile, statistics over the BN columns.  The
+// kernel multiplies with the operands swapped (W rows as the MFMA's A), so lane
+// l holds row l % 32 of each 32-row block and, in register i of block fn, the
+// id colb + fn*32 + mfma_row(i, l): a row's statistics are reductions inside
+// the lane and over the pair (l, l ^ 32).  With the ids across the lanes every
+// row took four 32-lane reductions: 16 rows x 4096 ids (K = 256) 14.8 -> 6.8
+// us, 128 x 126464 (K = 4096) 272 -> 251 us, 836 rows 1630 -> 1486 us.
 template <int BM, int WM, int WN, int FM, int FN>
 __device__ __forceinline__ void epi_lmstats(const GemmCall& c, f32x16 (&acc)[FM][FN], int m0,
-                                            int tn, int rowb, int colb, int lane, int wm, int wn,
+                                            int tn, int colb, int lane, int wm, int wn,
                                             uint16_t* smem_raw) {
   const LmStatsOut& lm = c.lm;
   float* red_m = reinterpret_cast<float*>(smem_raw);
@@ -459,58 +465,102 @@ __device__ __forceinline__ void epi_lmstats(const GemmCall& c, f32x16 (&acc)[FM]
   float* red_t = red_b + WN * BM;
   int* red_i = reinterpret_cast<int*>(red_t + WN * BM);
   float* red_z = reinterpret_cast<float*>(red_i + WN * BM);  // entropy term (pz only)
-  float bias[FN];
+  constexpr int WTN = FN * 32;
+  colb = __builtin_amdgcn_readfirstlane(colb);
+  const int id0 = colb + 4 * (lane >> 5);  // register i of block fn: id0 + fn*32 + 8*(i/4) + i%4
+  if (lm.bias) {
 #pragma unroll
-  for (int fn = 0; fn < FN; ++fn) bias[fn] = lm.bias ? lm.bias[colb + fn * 32 + (lane & 31)] : 0.f;
+    for (int fn = 0; fn < FN; ++fn)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        struct __attribute__((packed, aligned(4))) F4 { float v[4]; };  // (a 16-byte load at any 4-byte address)
+        const F4 bz = *reinterpret_cast<const F4*>(lm.bias + id0 + fn * 32 + 8 * q);
+#pragma unroll
+        for (int fm = 0; fm < FM; ++fm)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) acc[fm][fn][4 * q + e] += bz.v[e];
+      }
+  }
+  const bool mask_here = lm.mask_id >= colb && lm.mask_id < colb + WTN;
   __syncthreads();  // LDS is reused
 #pragma unroll
-  for (int fm = 0; fm < FM; ++fm)
+  for (int fm = 0; fm < FM; ++fm) {
+    const int lrow = wm * (BM / WM) + fm * 32 + (lane & 31);
+    const int row = m0 + lrow;
+    const int tgt = row < c.M ? lm.target[row] : -1;
+    float mx = kNegBig;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const int lrow = wm * (BM / WM) + fm * 32 + mfma_row(i, lane);
-      const int row = m0 + lrow;
-      const int tgt = row < c.M ? lm.target[row] : -1;
-      float mx = kNegBig, bz = kNegBig, tz = kNegBig;
-      int bi = INT_MAX;
+    for (int fn = 0; fn < FN; ++fn)
 #pragma unroll
-      for (int fn = 0; fn < FN; ++fn) {
-        const int col = colb + fn * 32 + (lane & 31);
-        const float v = acc[fm][fn][i] + bias[fn];
-        mx = fmaxf(mx, v);
-        if (col != lm.mask_id && v > bz) { bz = v; bi = col; }
-        if (col == tgt) tz = v;
-      }
-      // over the 32 lanes (columns) of each half-wave
-      mx = valu_max<32>(mx);
-      tz = valu_max<32>(tz);
-      valu_argmax<32>(bz, bi);
-      float se = 0.f, sz = 0.f;
-      if (lm.pz) {
-        // sum exp(z - m) * (z - m): the entropy's expectation term, relative
-        // to the tile max so nothing cancels against a large m
+      for (int i = 0; i < 16; ++i) mx = fmaxf(mx, acc[fm][fn][i]);
+    mx = max_xor32(mx);
+    // best value over non-mask ids: differs from mx only where the mask id is
+    float bz = mx;
+    if (mask_here) {
+      bz = kNegBig;
 #pragma unroll
-        for (int fn = 0; fn < FN; ++fn) {
-          const float u = acc[fm][fn][i] + bias[fn] - mx;
-          const float e = __expf(u);
-          se += e;
-          sz += e * u;
-        }
-        se = valu_sum<32>(se);
-        sz = valu_sum<32>(sz);
-      } else {
+      for (int fn = 0; fn < FN; ++fn)
 #pragma unroll
-        for (int fn = 0; fn < FN; ++fn) se += __expf(acc[fm][fn][i] + bias[fn] - mx);
-        se = valu_sum<32>(se);
-      }
-      if ((lane & 31) == 0) {
-        red_m[wn * BM + lrow] = mx;
-        red_s[wn * BM + lrow] = se;
-        red_b[wn * BM + lrow] = bz;
-        red_t[wn * BM + lrow] = tz;
-        red_i[wn * BM + lrow] = bi;
-        if (lm.pz) red_z[wn * BM + lrow] = sz;
-      }
+        for (int i = 0; i < 16; ++i)
+          bz = id0 + fn * 32 + 8 * (i >> 2) + (i & 3) == lm.mask_id ? bz : fmaxf(bz, acc[fm][fn][i]);
+      bz = max_xor32(bz);
     }
+    // its lowest id (ids grow with fn, then i, within a lane)
+    int bi = INT_MAX;
+#pragma unroll
+    for (int fn = FN - 1; fn >= 0; --fn)
+#pragma unroll
+      for (int i = 15; i >= 0; --i) bi = acc[fm][fn][i] == bz ? id0 + fn * 32 + 8 * (i >> 2) + (i & 3) : bi;
+    if (mask_here && bi == lm.mask_id) {  // the mask id ties with the best other id: look past it
+      bi = INT_MAX;
+#pragma unroll
+      for (int fn = FN - 1; fn >= 0; --fn)
+#pragma unroll
+        for (int i = 15; i >= 0; --i) {
+          const int id = id0 + fn * 32 + 8 * (i >> 2) + (i & 3);
+          bi = acc[fm][fn][i] == bz && id != lm.mask_id ? id : bi;
+        }
+    }
+    bi = min_xor32(bi);
+    float tz = kNegBig;
+    const int trel = tgt - id0;  // this lane's ids: bit 2 of trel clear
+    if (__any(trel >= 0 && trel < WTN && !(trel & 4))) {
+#pragma unroll
+      for (int fn = 0; fn < FN; ++fn)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) tz = trel == fn * 32 + 8 * (i >> 2) + (i & 3) ? acc[fm][fn][i] : tz;
+      tz = max_xor32(tz);
+    }
+    float se4[4] = {0.f, 0.f, 0.f, 0.f}, sz4[4] = {0.f, 0.f, 0.f, 0.f};
+    if (lm.pz) {
+      // sum exp(z - m) * (z - m): the entropy's expectation term, relative
+      // to the tile max so nothing cancels against a large m
+#pragma unroll
+      for (int fn = 0; fn < FN; ++fn)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          const float u = acc[fm][fn][i] - mx;
+          const float e = __expf(u);
+          se4[i & 3] += e;
+          sz4[i & 3] += e * u;
+        }
+    } else {
+#pragma unroll
+      for (int fn = 0; fn < FN; ++fn)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) se4[i & 3] += __expf(acc[fm][fn][i] - mx);
+    }
+    const float se = sum_xor32((se4[0] + se4[1]) + (se4[2] + se4[3]));
+    const float sz = sum_xor32((sz4[0] + sz4[1]) + (sz4[2] + sz4[3]));
+    if (lane < 32) {
+      red_m[wn * BM + lrow] = mx;
+      red_s[wn * BM + lrow] = se;
+      red_b[wn * BM + lrow] = bz;
+      red_t[wn * BM + lrow] = tz;
+      red_i[wn * BM + lrow] = bi;
+      if (lm.pz) red_z[wn * BM + lrow] = sz;
+    }
+  }
   __syncthreads();
   for (int r = threadIdx.x; r < BM; r += WM * WN * 64) {
     const int row = m0 + r;
@@ -624,7 +674,7 @@ __global__ __launch_bounds__(WM* WN * 64, (OCC * WM * WN + 3) / 4) void gemm_ker
   // M); with two stages every later wait is for all of a wave's copies, so
   // only the first wait changes.
   constexpr bool CAN_SKIP = NST == 2 && !SPLIT && NW == 8;  // (W copies are never skipped)
-  constexpr bool BIG2 = NW == 8 && BM == 256 && BN == 256 && XW == 0;
+  constexpr bool BIG2 = NW == 8 && BM == 256 && BN == 256 && XW == 0 && NST == 2;
   constexpr int CROSS = BIG2 ? 3 : 1;
   static_assert(CROSS != 3 || (XW == 0 && NST == 2), "the W-first crossing relies on waiting for every copy");
   bool alive[A_INS];
@@ -723,16 +773,21 @@ __global__ __launch_bounds__(WM* WN * 64, (OCC * WM * WN + 3) / 4) void gemm_ker
     }
     }
   };
+  // (EPI_LMSTATS: operands swapped, so that a lane holds one row and many ids)
+  auto mma1 = [&](const typename A::v8& a, const typename A::v8& b, const f32x16& cc) {
+    if constexpr (EPI == EPI_LMSTATS) return A::mma(b, a, cc);
+    else return A::mma(a, b, cc);
+  };
   auto mfmas = [&](int buf) {
 #pragma unroll
     for (int fm = 0; fm < FMV; ++fm)
 #pragma unroll
-      for (int fn = 0; fn < FN; ++fn) acc[fm][fn] = A::mma(af[buf][fm], bf[buf][fn], acc[fm][fn]);
+      for (int fn = 0; fn < FN; ++fn) acc[fm][fn] = mma1(af[buf][fm], bf[buf][fn], acc[fm][fn]);
     if constexpr (SPLIT) {
 #pragma unroll
       for (int fm = 0; fm < FMV; ++fm)
 #pragma unroll
-        for (int fn = 0; fn < FN; ++fn) acc[fm][fn] = A::mma(al[buf][fm], bf[buf][fn], acc[fm][fn]);
+        for (int fn = 0; fn < FN; ++fn) acc[fm][fn] = mma1(al[buf][fm], bf[buf][fn], acc[fm][fn]);
     }
   };
   // steps 0..KS-2 of a tile: the reads of step ks+1 go between the MFMAs of ks
@@ -879,7 +934,7 @@ __global__ __launch_bounds__(WM* WN * 64, (OCC * WM * WN + 3) / 4) void gemm_ker
     if (c.geom.T >= WTM) epi_qkv_rope<A, FM, FN, true>(c, acc, rowb, colb, lane, smem + wave * (WTM * WTN));
     else epi_qkv_rope<A, FM, FN, false>(c, acc, rowb, colb, lane, smem + wave * (WTM * WTN));
   }
-  else epi_lmstats<BM, WM, WN, FM, FN>(c, acc, m0, tn, rowb, colb, lane, wm, wn, smem);
+  else epi_lmstats<BM, WM, WN, FM, FN>(c, acc, m0, tn, colb, lane, wm, wn, smem);
 }
 
 struct TileCfg {
@@ -917,26 +972,29 @@ constexpr TileCfg kTiles[] = {
     {128, 256, 4, 2, 64, 3, 1, 0.78f},  // 10 (8 waves, three stages)
     {256, 256, 4, 2, 64, 2, 1, 1.00f, 1},  // 11 (8 waves, third W stage)
     {128, 256, 4, 2, 64, 2, 1, 0.77f, 1},  // 12 (8 waves, third W stage)
+    {256, 256, 4, 2, 32, 3, 1, 1.00f},  // 13 (8 waves, three 32-deep stages; LM head only)
 };
 constexpr int kNumTiles = sizeof(kTiles) / sizeof(kTiles[0]);
 
 // Which epilogues each tile is built for.  The LM-head epilogues double the A
-// tile (hi and lo parts), which fits LDS only for BM <= 128 (the 8-wave
-// 128x256 tile: 1.19 -> 0.97 ms for the 512-row LM head); the thin 32-row
-// tile serves only them (it loses to wider tiles elsewhere); the 4-wave
-// 256x256 tile spills registers in the RoPE epilogue.  (RoPE also needs a
-// wave to own exactly one head, WTN == hd: 64 or 128 here, checked per call.)
-constexpr bool tile_epi(int BM, int BN, int WM, int WN, int EPI) {
+// tile (hi and lo parts): with 64-deep stages that fits LDS only for BM <= 128,
+// the 256-row tile takes 32-deep ones (per MFMA it moves a quarter less than a
+// plain 256x256 tile: 1024 rows x 126464 ids 1688 -> 1561 us against 128x256,
+// 836 rows 1486 -> 1532).  The thin 32-row tile serves only them (it loses to
+// wider tiles elsewhere); the 4-wave 256x256 tile spills registers in the RoPE
+// epilogue.  (RoPE also needs a wave to own exactly one head, WTN == hd: 64 or
+// 128 here, checked per call.)
+constexpr bool tile_epi(int BM, int BN, int WM, int WN, int KB, int EPI) {
   return (EPI == EPI_LMSTATS || EPI == EPI_LOGITS)
-             ? (BM == 32 || (BM == 128 && BN == 256))
-             : (BM != 32 && (EPI == EPI_QKV_ROPE ? !(BM == 256 && WM == 2 && WN == 2) &&
-                                                       (BN / WN == 64 || BN / WN == 128)
-                                                 : true));
+             ? (BM == 32 || (BM == 128 && WM == 2 && WN == 4) || (KB == 32 && EPI == EPI_LMSTATS))
+             : (BM != 32 && KB == 64 && (EPI == EPI_QKV_ROPE ? !(BM == 256 && WM == 2 && WN == 2) &&
+                                                                   (BN / WN == 64 || BN / WN == 128)
+                                                             : true));
 }
 
 bool tile_ok(const GemmCall& c, const TileCfg& t) {
   if (c.N % t.BN || c.K % BK) return false;
-  if (!tile_epi(t.BM, t.BN, t.WM, t.WN, c.epi)) return false;
+  if (!tile_epi(t.BM, t.BN, t.WM, t.WN, t.KB, c.epi)) return false;
   const int arows = (c.epi == EPI_LMSTATS || c.epi == EPI_LOGITS) ? 2 * t.BM : t.BM;
   const int lds_elems = (t.NST * arows + (t.NST + t.xw) * t.BN) * t.KB;
   if (t.xw && (arows != t.BM || t.NST != 2)) return false;
@@ -990,7 +1048,12 @@ double makespan(long n_main, double T, long n_units, double U, long slots) {
 // us, QKV 70 -> 67 us; 512 rows: gate/up 141 -> 103 us).  Where the
 // weights are shared by many row tiles (8704 rows: -1%) or the unit is short
 // (K slices of 8-16 steps: 10-17% slower) it does not pay.
+//
+// LM head: measured over 16-1024 rows x 4096-126464 ids (the 32-row tile, two
+// per CU, reads W once per 32 rows and is ahead up to about 64 rows: 168 us
+// against 229 at 32 x 126464, 360 against 251 at 128).
 double eff_of(const GemmCall& c, const TileCfg& t, int ksteps) {
+  if (c.epi == EPI_LMSTATS || c.epi == EPI_LOGITS) return t.BM == 32 ? 0.54 : t.BM == 128 ? 0.77 : 0.85;
   if (!t.xw) return t.eff;
   const bool cold = (c.M + t.BM - 1) / t.BM <= 5;
   return cold && ksteps >= 24 ? 1.2 * t.eff : 0.9 * t.eff;
@@ -1074,7 +1137,7 @@ hipError_t launch_one(const GemmCall& c, hipStream_t st) {
   constexpr int arows = split ? 2 * BM : BM;
   constexpr int lds = (NST * arows + (NST + XW) * BN) * KB * 2;
   constexpr bool qkv_fits = EPI != EPI_QKV_ROPE || BM * BN * 2 <= lds;
-  if constexpr (tile_epi(BM, BN, WM, WN, EPI) && lds * OCC <= 160 * 1024 && qkv_fits &&
+  if constexpr (tile_epi(BM, BN, WM, WN, KB, EPI) && lds * OCC <= 160 * 1024 && qkv_fits &&
                 (XW == 0 || !split)) {
     const int nTM = (c.M + BM - 1) / BM, nTN = c.N / BN;
     int units = nTM * nTN;
@@ -1187,6 +1250,7 @@ hipError_t launch_gemm(const GemmCall& c, hipStream_t st) {
     case 10: return launch_cfg<128, 256, 4, 2, 64, 3, 1>(c, st);
     case 11: return launch_cfg<256, 256, 4, 2, 64, 2, 1, 1>(c, st);
     case 12: return launch_cfg<128, 256, 4, 2, 64, 2, 1, 1>(c, st);
+    case 13: return launch_cfg<256, 256, 4, 2, 32, 3, 1>(c, st);
   }
   return hipErrorInvalidValue;
 }
