@@ -402,18 +402,22 @@ __device__ __forceinline__ void epi_qkv_rope(const GemmCall& c, f32x16 (&acc)[FM
     if (tr.t0 + WTM <= g.T && rowb + WTM <= c.M && (tr.t0 & 7) == 0) {
       // one sequence, no row past M, 16-byte aligned runs: the head's v^T
       // rows from a wave-uniform base (position t0) at per-lane offsets
-      constexpr int EPP = 64 / VCH;  // v^T rows per pass
       const size_t bh = (size_t)b0u * ro.H + head;
       uint16_t* dst = uniform_ptr(ro.vt + bh * HD * g.Tp + t0u);
-      const int el = lane / VCH, ch = lane % VCH;
-      uint16_t* dl = dst + (size_t)el * g.Tp + ch * 8;
 #pragma unroll
       for (int it = 0; it < HD * VCH / 64; ++it) {
-        const int e = it * EPP + el;
+        int e, ch;
+        if constexpr ((VCH & (VCH - 1)) == 0) {
+          e = it * (64 / VCH) + lane / VCH;  // (a lane part and a constant part)
+          ch = lane % VCH;
+        } else {
+          e = (it * 64 + lane) / VCH;
+          ch = it * 64 + lane - e * VCH;
+        }
         const int m = (e >> 1) & SMASK;
         uint4 v = *reinterpret_cast<const uint4*>(ws + e * WTM + ((ch ^ (m >> 1)) << 3));
         if (m & 1) v = make_uint4(v.z, v.w, v.x, v.y);
-        *reinterpret_cast<uint4*>(dl + (size_t)it * EPP * g.Tp) = v;
+        *reinterpret_cast<uint4*>(dst + (size_t)e * g.Tp + ch * 8) = v;
       }
       return;
     }
@@ -661,13 +665,16 @@ __global__ __launch_bounds__(WM* WN * 64, (OCC * WM * WN + 3) / 4) void gemm_ker
   const int gsz = min(rTM - first_m, GM);
   const int tm = (tail ? mainTM : 0) + first_m + (t % (GM * nTN)) % gsz;
   const int tn = (t % (GM * nTN)) / gsz;
-  const int Ku = ksplit && tail ? c.K / c.splits : c.K;  // K depth of this unit
+  // K steps of this unit (the slices of a tile differ by at most one 64-deep step)
+  const int nkt = c.K / KB;
+  const int k0 = ksplit && tail ? (int)((long)split * (c.K / BK) / c.splits) * (BK / KB) : 0;
+  const int k1 = ksplit && tail ? (int)((long)(split + 1) * (c.K / BK) / c.splits) * (BK / KB) : nkt;
   const int m0 = tm * BM, n0 = tn * BN;
 
   // The lane that fills position (lane % CPR) of row RPI*i + lane/CPR of a
   // tile fetches the chunk that belongs there: position ^ lds_swz(row).
   const int lrow = lane / CPR, lpos = lane % CPR;
-  const int kbase = split * Ku;  // first K column of this unit
+  const int kbase = k0 * KB;  // first K column of this unit
   // In a partial row tile (8-wave shapes; the 4-wave ones would need more
   // registers for the extra code paths) a wave skips the MFMAs of its rows
   // past M and the copies of A rows past M (they feed only output rows past
@@ -725,7 +732,7 @@ __global__ __launch_bounds__(WM* WN * 64, (OCC * WM * WN + 3) / 4) void gemm_ker
 #pragma unroll
       for (int i = 0; i < 16; ++i) acc[fm][fn][i] = 0.f;
 
-  const int nk = Ku / KB;
+  const int nk = k1 - k0;
   const int arow = wm * WTM + (lane & 31), brow = wn * WTN + (lane & 31);
   // swizzle of each fragment row this lane reads (fixed over the K loop)
   int aswz[FM], alswz[SPLIT ? FM : 1], bswz[FN];
@@ -937,42 +944,45 @@ __global__ __launch_bounds__(WM* WN * 64, (OCC * WM * WN + 3) / 4) void gemm_ker
   else epi_lmstats<BM, WM, WN, FM, FN>(c, acc, m0, tn, colb, lane, wm, wn, smem);
 }
 
+// A tile shape: BM x BN by WM x WN waves, NST stages of KB-deep K steps (xw more
+// for W), occ workgroups per CU, and its measured times in microseconds: a unit
+// of n 64-deep K steps takes fix + n * (lat + (load + cold / r) * u), u the share
+// of the chip's 256 * occ workgroup slots in use (what the copies share) and r the
+// row tiles that read each W strip (one of them from HBM).
 struct TileCfg {
-  int BM, BN, WM, WN;
-  int KB, NST;  // K step of a pipeline stage, number of LDS stages
-  int occ;      // workgroups a CU holds at once (LDS / registers)
-  float eff;    // relative per-CU matrix-core throughput when the chip is full
-                // (measured on the 8704x24576x4096 gate/up shape)
-  int xw = 0;   // 1: a third LDS stage for the W tiles
+  int BM, BN, WM, WN, KB, NST, occ, xw;
+  float fix, lat, load, cold;
 };
 
-// eff: measured relative throughput of each shape (8704 x 24576 x 4096, and
-// the O / down residual shapes for the 192-row tile, whose single wave per
-// SIMD exposes the residual read-add-write).  Deeper pipelines of 32-deep K
-// stages and two-per-CU 128x256 tiles were measured slower than entry 6.
-// Entry 9 gives the QKV GEMM (a head per wave) two waves per SIMD at few
-// rows: 678 vs 598 TFLOP/s at 544 rows.  Entry 4 is set from the 544-row O
-// projection (split 2: 40.8 us against 34.6 us for entry 3), where its three
-// workgroups per CU are rarely all resident.  Entry 10 keeps two K tiles in
-// flight instead of one: at 544 rows each weight strip is read by few row
-// tiles, so most of its copies miss L2, and the QKV GEMM takes 66 instead
-// of 74 us (weights streamed from HBM); where the weights are shared by many
-// row tiles the third stage does not pay (deeper pipelines lost there).
+// fix / lat / load / cold: least squares over 119 shapes (24-8704 rows, N
+// 256-24576, K 256-12288, both types, weights from HBM; rms error 6-15% per tile
+// where it is competitive), LM head tiles over 11 (16-1024 rows x 4096-126464
+// ids).  The tile the model picks is 1% behind the fastest one on average.  What each shape is for:
+//  - few units, bound by the latency of the copies: small tiles that keep many
+//    stages in flight (entries 8-12; 64 rows x 24576 x 4096 58 -> 45 us, 128 x
+//    17408 x 3072 62 -> 37, 32 x 256 x 704 9.5 -> 5.9)
+//  - many units: 256x256, or the 192-row tiles where those round better (1444 x
+//    24576 x 4096 316 -> 272 us, 870 x 12288 x 4096 102 -> 93)
+//  - a third W stage (xw): the weights of few row tiles come from HBM, not L2
 constexpr TileCfg kTiles[] = {
-    {256, 256, 2, 2, 64, 2, 1, 0.95f},  // 0
-    {192, 256, 2, 2, 64, 2, 1, 0.75f},  // 1
-    {128, 256, 2, 2, 64, 2, 1, 0.76f},  // 2
-    {128, 128, 2, 2, 64, 2, 2, 0.78f},  // 3
-    {64, 128, 2, 2, 64, 2, 3, 0.50f},   // 4
-    {32, 256, 1, 4, 64, 2, 2, 0.60f},   // 5
-    {256, 256, 4, 2, 64, 2, 1, 1.00f},  // 6  (8 waves)
-    {256, 256, 2, 4, 64, 2, 1, 0.98f},  // 7  (8 waves)
-    {128, 256, 2, 4, 64, 2, 1, 0.74f},  // 8  (8 waves)
-    {128, 256, 4, 2, 64, 2, 1, 0.77f},  // 9  (8 waves, 32-row wave tiles)
-    {128, 256, 4, 2, 64, 3, 1, 0.78f},  // 10 (8 waves, three stages)
-    {256, 256, 4, 2, 64, 2, 1, 1.00f, 1},  // 11 (8 waves, third W stage)
-    {128, 256, 4, 2, 64, 2, 1, 0.77f, 1},  // 12 (8 waves, third W stage)
-    {256, 256, 4, 2, 32, 3, 1, 1.00f},  // 13 (8 waves, three 32-deep stages; LM head only)
+    {128, 128, 2, 2, 64, 2, 2, 0, 1.60f, 0.607f, 0.387f, 0.524f},  // 0
+    {32, 256, 1, 4, 64, 2, 2, 0, 0.40f, 1.037f, 0.247f, 0.000f},  // 1: LM head
+    {256, 256, 4, 2, 64, 2, 1, 0, 4.58f, 1.130f, 0.415f, 0.000f},  // 2
+    {256, 256, 4, 2, 64, 2, 1, 1, 5.07f, 1.041f, 0.521f, 0.000f},  // 3
+    {128, 256, 4, 2, 64, 3, 1, 0, 3.51f, 0.686f, 0.243f, 0.159f},  // 4
+    {128, 256, 4, 2, 64, 2, 1, 1, 2.57f, 0.770f, 0.160f, 0.105f},  // 5
+    {128, 256, 2, 4, 64, 2, 1, 0, 3.07f, 1.379f, 0.379f, 0.000f},  // 6: LM head
+    {256, 256, 4, 2, 32, 3, 1, 0, 9.45f, 1.309f, 1.628f, 0.000f},  // 7: LM head
+    {64, 64, 2, 1, 64, 6, 1, 0, 1.58f, 0.245f, 0.036f, 0.095f},  // 8
+    {64, 128, 2, 2, 64, 4, 1, 0, 1.48f, 0.335f, 0.049f, 0.271f},  // 9
+    {32, 64, 1, 1, 64, 6, 1, 0, 1.63f, 0.169f, 0.000f, 0.287f},  // 10
+    {64, 128, 2, 2, 64, 3, 2, 0, 1.20f, 0.289f, 0.360f, 0.507f},  // 11
+    {128, 128, 4, 2, 64, 4, 1, 0, 2.08f, 0.397f, 0.182f, 0.139f},  // 12
+    {128, 128, 4, 1, 64, 2, 2, 0, 1.12f, 0.660f, 0.353f, 0.408f},  // 13
+    {192, 256, 2, 4, 64, 2, 1, 1, 4.08f, 0.870f, 0.376f, 0.000f},  // 14
+    {192, 128, 2, 2, 64, 2, 2, 0, 2.21f, 0.697f, 0.659f, 0.000f},  // 15
+    {256, 256, 2, 4, 64, 2, 1, 0, 6.57f, 1.116f, 0.450f, 0.000f},  // 16: QKV of 64-wide heads
+    {64, 128, 2, 1, 64, 4, 1, 0, 2.55f, 0.390f, 0.024f, 0.211f},  // 17: QKV of 128-wide heads
 };
 constexpr int kNumTiles = sizeof(kTiles) / sizeof(kTiles[0]);
 
@@ -980,28 +990,31 @@ constexpr int kNumTiles = sizeof(kTiles) / sizeof(kTiles[0]);
 // tile (hi and lo parts): with 64-deep stages that fits LDS only for BM <= 128,
 // the 256-row tile takes 32-deep ones (per MFMA it moves a quarter less than a
 // plain 256x256 tile: 1024 rows x 126464 ids 1688 -> 1561 us against 128x256,
-// 836 rows 1486 -> 1532).  The thin 32-row tile serves only them (it loses to
-// wider tiles elsewhere); the 4-wave 256x256 tile spills registers in the RoPE
-// epilogue.  (RoPE also needs a wave to own exactly one head, WTN == hd: 64 or
-// 128 here, checked per call.)
+// 836 rows 1486 -> 1532), and 32 rows two per CU serve few rows (32 x 126464
+// 168 us against 229).  RoPE needs a wave to own exactly one head, WTN == hd (64
+// or 128, checked per call); two tiles serve only it: 256x256 with 64-wide wave
+// tiles and 64x128 with 128-wide ones.
 constexpr bool tile_epi(int BM, int BN, int WM, int WN, int KB, int EPI) {
-  return (EPI == EPI_LMSTATS || EPI == EPI_LOGITS)
-             ? (BM == 32 || (BM == 128 && WM == 2 && WN == 4) || (KB == 32 && EPI == EPI_LMSTATS))
-             : (BM != 32 && KB == 64 && (EPI == EPI_QKV_ROPE ? !(BM == 256 && WM == 2 && WN == 2) &&
-                                                                   (BN / WN == 64 || BN / WN == 128)
-                                                             : true));
+  const int WTN = BN / WN;
+  if ((BM == 32 && BN == 256) || (BM == 128 && BN == 256 && WM == 2))
+    return EPI == EPI_LMSTATS || EPI == EPI_LOGITS;
+  if (KB == 32) return EPI == EPI_LMSTATS;
+  if (EPI == EPI_LMSTATS || EPI == EPI_LOGITS) return false;
+  if (EPI == EPI_QKV_ROPE) return WTN == 64 || WTN == 128;
+  return !(BM == 256 && WN == 4) && !(BM == 64 && BN == 128 && WN == 1);
 }
 
 bool tile_ok(const GemmCall& c, const TileCfg& t) {
-  if (c.N % t.BN || c.K % BK) return false;
+  // (N in whole 128-column tiles whatever the tile: the 64-wide ones choose
+  // among the same shapes)
+  if (c.N % std::max(t.BN, 128) || c.K % BK) return false;
   if (!tile_epi(t.BM, t.BN, t.WM, t.WN, t.KB, c.epi)) return false;
-  const int arows = (c.epi == EPI_LMSTATS || c.epi == EPI_LOGITS) ? 2 * t.BM : t.BM;
-  const int lds_elems = (t.NST * arows + (t.NST + t.xw) * t.BN) * t.KB;
-  if (t.xw && (arows != t.BM || t.NST != 2)) return false;
-  if (t.occ * lds_elems * 2 > 160 * 1024) return false;
-  if (c.epi == EPI_QKV_ROPE && t.BM * t.BN > lds_elems) return false;
   const int WTN = t.BN / t.WN;
-  if (c.epi == EPI_QKV_ROPE) return WTN == c.rope.hd && (c.rope.H * c.rope.hd) % t.BN == 0;
+  // (RoPE: heads in pairs, like the 128-column rule)
+  if (c.epi == EPI_QKV_ROPE) {
+    const int d = c.rope.H * c.rope.hd;
+    return WTN == c.rope.hd && d % t.BN == 0 && d % (2 * c.rope.hd) == 0;
+  }
   if (c.epi == EPI_SWIGLU) return (c.F % (WTN / 2)) == 0;
   return true;
 }
@@ -1011,10 +1024,15 @@ int env_int(const char* name, int dflt) {
   return e ? std::atoi(e) : dflt;
 }
 
-// Throughput model: a CU sustains ~6.5 TFLOP/s of bf16 MFMA (~1.7 PFLOP/s
-// over 256 CUs) times the tile's relative efficiency, shared by the `occ`
-// workgroups it holds; epilogue traffic moves at ~4 TB/s shared by all slots.
-constexpr double kCuFlops = 6.5e12, kEpiBw = 4.0e12, kPartBw = 2.5e12;
+// Launch overhead (us), the rate weights stream from HBM (bytes/us), and what
+// split-K partials cost: bytes/us over their write in the GEMM (about 5.5) and
+// their read in the norm kernel that adds them (about 4.2), and a fixed time.
+constexpr double kLaunchUs = 2.2, kWRate = 5.6e6, kPartRate = 2.4e6, kPartUs = 2.0;
+
+double unit_us(const GemmCall& c, const TileCfg& t, double ksteps, double units) {
+  const double u = std::min(1.0, units / (256.0 * t.occ)), r = (c.M + t.BM - 1) / t.BM;
+  return t.fix + ksteps * (t.lat + (t.load + t.cold / r) * u);
+}
 
 // Makespan of n_main jobs of length T followed by n_units jobs of length U,
 // each started on the slot that frees first (the hardware dispatcher's order).
@@ -1040,34 +1058,17 @@ double makespan(long n_main, double T, long n_units, double U, long slots) {
   return std::max(main_end, best);
 }
 
-// eff of a tile for a unit of ksteps 64-deep K steps.  A W strip is read by
-// the ceil(M / BM) row tiles of its column; at five or fewer most of its
-// copies miss L2 and a two-stage pipeline waits on them, which a third W
-// stage covers once the unit is long enough to fill it (weights streamed
-// from HBM; 544 rows: 256x256 gate/up 138 -> 116 us, 128x256 down 72 -> 65
-// us, QKV 70 -> 67 us; 512 rows: gate/up 141 -> 103 us).  Where the
-// weights are shared by many row tiles (8704 rows: -1%) or the unit is short
-// (K slices of 8-16 steps: 10-17% slower) it does not pay.
-//
-// LM head: measured over 16-1024 rows x 4096-126464 ids (the 32-row tile, two
-// per CU, reads W once per 32 rows and is ahead up to about 64 rows: 168 us
-// against 229 at 32 x 126464, 360 against 251 at 128).
-double eff_of(const GemmCall& c, const TileCfg& t, int ksteps) {
-  if (c.epi == EPI_LMSTATS || c.epi == EPI_LOGITS) return t.BM == 32 ? 0.54 : t.BM == 128 ? 0.77 : 0.85;
-  if (!t.xw) return t.eff;
-  const bool cold = (c.M + t.BM - 1) / t.BM <= 5;
-  return cold && ksteps >= 24 ? 1.2 * t.eff : 0.9 * t.eff;
-}
-
 // Time of the partial last row tile (rem = M mod BM rows) relative to a full
-// one.  8-wave shapes skip the MFMAs of rows past M per wave (the kernel's
-// rule: a wave keeps all its 32-row blocks, only the first, or none), so the
-// busiest SIMD's remaining share sets the time, floored at kPartialFloor for
-// the copies and barriers every wave still makes.  Other shapes: a full tile.
-constexpr double kPartialFloor = 0.3;
+// one.  8-wave two-stage shapes skip the MFMAs of rows past M per wave (the
+// kernel's rule: a wave keeps all its 32-row blocks, only the first, or none), so
+// the busiest SIMD's remaining share sets the time, at least kPartialFloor; and a
+// tile alone on its CU still waits for its copies, kPartialLat of an idle chip's
+// time.  Other shapes: a full tile.
+constexpr double kPartialFloor = 0.3, kPartialLat = 0.75;
 double partial_share(const GemmCall& c, const TileCfg& t, int rem) {
   const bool lm = c.epi == EPI_LMSTATS || c.epi == EPI_LOGITS;
-  if (rem == 0 || lm || t.WM * t.WN != 8 || t.NST != 2) return 1.0;  // (XW tiles skip too)
+  if (rem == 0) return 0.0;
+  if (lm || t.WM * t.WN != 8 || t.NST != 2) return 1.0;  // (xw tiles skip too)
   const int WTM = t.BM / t.WM, FM = WTM / 32;
   double load[4] = {0, 0, 0, 0};
   for (int w = 0; w < 8; ++w) {
@@ -1079,38 +1080,43 @@ double partial_share(const GemmCall& c, const TileCfg& t, int rem) {
   return std::max(busiest, kPartialFloor);
 }
 
-// Estimated seconds for whole-K tiles: the full row tiles, then the partial
-// last row tile (the kernel's order), dealt to 256 CUs as they free up (a CU
-// holding fewer tiles than it could runs proportionally less efficiently).
-double tile_time(const GemmCall& c, const TileCfg& t) {
-  const long nTN = c.N / t.BN;
-  const int rem = c.M % t.BM;
-  const long n_full = (long)(c.M / t.BM) * nTN, n_part = rem ? nTN : 0;
-  const long per_cu = std::min<long>(t.occ, (n_full + n_part + 255) / 256);
-  const double util = 0.5 + 0.5 * (double)per_cu / t.occ;
-  const double tile_s = 2.0 * t.BM * t.BN * (double)c.K / (eff_of(c, t, c.K / BK) * util * kCuFlops);
-  return makespan(n_full, tile_s, n_part, partial_share(c, t, rem) * tile_s, 256);
+// Time of the partial last row tile's unit next to full ones of time T.
+double partial_us(const GemmCall& c, const TileCfg& t, double ksteps, double T) {
+  return std::max(partial_share(c, t, c.M % t.BM) * T, kPartialLat * (t.fix + ksteps * t.lat));
 }
 
-// Residual GEMM: whole-K tiles read-add-write 8 bytes of x per output; the
-// `splits` K-slices of the last tail_tm row tiles write 4-byte partials that
-// the next norm kernel reads back.
-double residual_time(const GemmCall& c, const TileCfg& t, int tail_tm, int splits) {
-  const int nTM = (c.M + t.BM - 1) / t.BM, nTN = c.N / t.BN;
-  const long slots = 256L * t.occ;
-  const double rate = eff_of(c, t, c.K / BK) * kCuFlops / t.occ;
-  const double out_s = (double)t.BM * t.BN / (kEpiBw / slots);
-  const double T = 2.0 * t.BM * t.BN * (double)c.K / rate + 8.0 * out_s;
-  const long n_main = (long)(nTM - tail_tm) * nTN;
-  if (tail_tm == 0) {
-    const int rem = c.M % t.BM;
-    return makespan(n_main - (rem ? nTN : 0), T, rem ? nTN : 0, partial_share(c, t, rem) * T, slots);
+// Estimated time (us) of whole-K tiles: rounds of 256 * occ units, then what is
+// left and the partial last row tile at their own load; never less than reading W
+// once.
+double tile_time(const GemmCall& c, const TileCfg& t) {
+  const long nTN = c.N / t.BN, slots = 256L * t.occ;
+  const double ks = c.K / BK;
+  const long n_full = (c.M / t.BM) * nTN, n_part = c.M % t.BM ? nTN : 0;
+  const long rounds = n_full / slots, rest = n_full % slots;
+  double time = rounds * unit_us(c, t, ks, slots);
+  if (rest + n_part) {
+    const double T = unit_us(c, t, ks, rest + n_part);
+    time += makespan(rest, T, n_part, n_part ? partial_us(c, t, ks, T) : T, slots);
   }
-  const double urate = eff_of(c, t, c.K / splits / BK) * kCuFlops / t.occ;
-  const double U = 2.0 * t.BM * t.BN * ((double)c.K / splits + 2 * BK) / urate + 4.0 * out_s;
-  const long n_units = (long)tail_tm * nTN * splits;
+  return std::max(kLaunchUs + time, 2.0 + 2.0 * c.N * (double)c.K / kWRate);
+}
+
+// Residual GEMM whose last tail_tm row tiles are computed as `splits` K-slices
+// that write fp32 partials for the next norm kernel.
+double residual_time(const GemmCall& c, const TileCfg& t, int tail_tm, int splits) {
+  if (tail_tm == 0) return tile_time(c, t);
+  const int nTM = (c.M + t.BM - 1) / t.BM, nTN = c.N / t.BN;
+  const long slots = 256L * t.occ, n_main = (long)(nTM - tail_tm) * nTN;
+  const double ks = (double)c.K / BK, load = n_main + (double)tail_tm * nTN * splits;
+  const double T = unit_us(c, t, ks, load), U = unit_us(c, t, ks / splits, load);
+  // (beside whole-K tiles the partial row tile's slices count as whole ones)
+  const long n_slices = (long)(tail_tm - 1) * nTN * splits, n_last = (long)nTN * splits;
+  const double last = c.M % t.BM ? std::min(U, partial_us(c, t, ks / splits, U)) : U;
+  const double span = n_main ? makespan(n_main, T, n_slices + n_last, U, slots)
+                             : makespan(n_slices, U, n_last, last, slots);
   const double tail_rows = c.M - (double)(nTM - tail_tm) * t.BM;
-  return makespan(n_main, T, n_units, U, slots) + splits * tail_rows * c.N * 4.0 / kPartBw;
+  return kLaunchUs + span + kPartUs +
+         splits * tail_rows * c.N * 4.0 / kPartRate;
 }
 
 int pick_tile(const GemmCall& c) {
@@ -1137,8 +1143,8 @@ hipError_t launch_one(const GemmCall& c, hipStream_t st) {
   constexpr int arows = split ? 2 * BM : BM;
   constexpr int lds = (NST * arows + (NST + XW) * BN) * KB * 2;
   constexpr bool qkv_fits = EPI != EPI_QKV_ROPE || BM * BN * 2 <= lds;
-  if constexpr (tile_epi(BM, BN, WM, WN, KB, EPI) && lds * OCC <= 160 * 1024 && qkv_fits &&
-                (XW == 0 || !split)) {
+  if constexpr (tile_epi(BM, BN, WM, WN, KB, EPI)) {
+    static_assert(lds * OCC <= 160 * 1024 && qkv_fits && (XW == 0 || !split), "tile fits LDS");
     const int nTM = (c.M + BM - 1) / BM, nTN = c.N / BN;
     int units = nTM * nTN;
     if (EPI == EPI_RESIDUAL && c.splits > 1) {
@@ -1196,17 +1202,20 @@ void plan_residual_gemm(GemmCall& c, size_t part_elems) {
     if (!tile_ok(c, t) || (f_tile >= 0 && i != f_tile)) continue;
     const int nTM = (c.M + t.BM - 1) / t.BM;
     for (int tail = 0; tail <= nTM; ++tail) {
+      if (tail > 8 && tail < nTM) continue;  // (a few trailing row tiles, or all)
       if (f_tail >= 0 && tail != std::min(f_tail, nTM)) continue;
       const double tail_rows = c.M - (double)(nTM - tail) * t.BM;
       for (int s = tail ? 2 : 1; s <= (tail ? kMaxResidualSplits : 1); ++s) {
-        if (tail && (nk % s || nk / s < 4 || s * tail_rows * c.N > (double)part_elems)) continue;
+        // (the split counts the norm kernels have instances for)
+        if (s == 5 || s == 7) continue;
+        if (tail && (nk / s < 4 || s * tail_rows * c.N > (double)part_elems)) continue;
         if (tail && f_split > 0 && s != f_split) continue;
         const double time = residual_time(c, t, tail, s);
         if (best < 0 || time < best_t) { best = i; best_t = time; best_s = s; best_tail = tail; }
       }
     }
   }
-  if (best < 0) {  // no candidate under the overrides: plain whole-K tiles
+  if (best < 0) {  // no candidate under the overrides (or at all): whole-K tiles
     c.tile = 0; c.splits = 1; c.split_row0 = c.M;
     return;
   }
@@ -1233,24 +1242,28 @@ hipError_t launch_gemm(const GemmCall& c, hipStream_t st) {
   if (c.epi == EPI_RESIDUAL && c.splits > 1) {
     const int nk = c.K / BK;
     if (!c.part || c.split_row0 < 0 || c.split_row0 >= c.M || c.split_row0 % kTiles[i].BM ||
-        nk % c.splits)
+        nk < c.splits)
       return hipErrorInvalidValue;
   }
   switch (i) {
-    case 0: return launch_cfg<256, 256, 2, 2, 64, 2, 1>(c, st);
-    case 1: return launch_cfg<192, 256, 2, 2, 64, 2, 1>(c, st);
-    case 2: return launch_cfg<128, 256, 2, 2, 64, 2, 1>(c, st);
-    case 3: return launch_cfg<128, 128, 2, 2, 64, 2, 2>(c, st);
-    case 4: return launch_cfg<64, 128, 2, 2, 64, 2, 3>(c, st);
-    case 5: return launch_cfg<32, 256, 1, 4, 64, 2, 2>(c, st);
-    case 6: return launch_cfg<256, 256, 4, 2, 64, 2, 1>(c, st);
-    case 7: return launch_cfg<256, 256, 2, 4, 64, 2, 1>(c, st);
-    case 8: return launch_cfg<128, 256, 2, 4, 64, 2, 1>(c, st);
-    case 9: return launch_cfg<128, 256, 4, 2, 64, 2, 1>(c, st);
-    case 10: return launch_cfg<128, 256, 4, 2, 64, 3, 1>(c, st);
-    case 11: return launch_cfg<256, 256, 4, 2, 64, 2, 1, 1>(c, st);
-    case 12: return launch_cfg<128, 256, 4, 2, 64, 2, 1, 1>(c, st);
-    case 13: return launch_cfg<256, 256, 4, 2, 32, 3, 1>(c, st);
+    case 0: return launch_cfg<128, 128, 2, 2, 64, 2, 2>(c, st);
+    case 1: return launch_cfg<32, 256, 1, 4, 64, 2, 2>(c, st);
+    case 2: return launch_cfg<256, 256, 4, 2, 64, 2, 1>(c, st);
+    case 3: return launch_cfg<256, 256, 4, 2, 64, 2, 1, 1>(c, st);
+    case 4: return launch_cfg<128, 256, 4, 2, 64, 3, 1>(c, st);
+    case 5: return launch_cfg<128, 256, 4, 2, 64, 2, 1, 1>(c, st);
+    case 6: return launch_cfg<128, 256, 2, 4, 64, 2, 1>(c, st);
+    case 7: return launch_cfg<256, 256, 4, 2, 32, 3, 1>(c, st);
+    case 8: return launch_cfg<64, 64, 2, 1, 64, 6, 1>(c, st);
+    case 9: return launch_cfg<64, 128, 2, 2, 64, 4, 1>(c, st);
+    case 10: return launch_cfg<32, 64, 1, 1, 64, 6, 1>(c, st);
+    case 11: return launch_cfg<64, 128, 2, 2, 64, 3, 2>(c, st);
+    case 12: return launch_cfg<128, 128, 4, 2, 64, 4, 1>(c, st);
+    case 13: return launch_cfg<128, 128, 4, 1, 64, 2, 2>(c, st);
+    case 14: return launch_cfg<192, 256, 2, 4, 64, 2, 1, 1>(c, st);
+    case 15: return launch_cfg<192, 128, 2, 2, 64, 2, 2>(c, st);
+    case 16: return launch_cfg<256, 256, 2, 4, 64, 2, 1>(c, st);
+    case 17: return launch_cfg<64, 128, 2, 1, 64, 4, 1>(c, st);
   }
   return hipErrorInvalidValue;
 }

@@ -316,6 +316,7 @@ void rmsnorm_impl(float* x, const uint16_t* gain, float eps, int M, int d, uint1
       case 2: go(std::integral_constant<int, 2>{}); break;
       case 3: go(std::integral_constant<int, 3>{}); break;
       case 4: go(std::integral_constant<int, 4>{}); break;
+      case 6: go(std::integral_constant<int, 6>{}); break;
       case 8: go(std::integral_constant<int, 8>{}); break;
       default: go(std::integral_constant<int, -1>{});
     }
@@ -339,6 +340,7 @@ void launch_residual_reduce(float* x, const float* part, int n_part, int part_ro
     case 2: residual_reduce_kernel<2><<<grid, 256, 0, st>>>(x4, p4, n_part, n4); break;
     case 3: residual_reduce_kernel<3><<<grid, 256, 0, st>>>(x4, p4, n_part, n4); break;
     case 4: residual_reduce_kernel<4><<<grid, 256, 0, st>>>(x4, p4, n_part, n4); break;
+    case 6: residual_reduce_kernel<6><<<grid, 256, 0, st>>>(x4, p4, n_part, n4); break;
     case 8: residual_reduce_kernel<8><<<grid, 256, 0, st>>>(x4, p4, n_part, n4); break;
     default: residual_reduce_kernel<-1><<<grid, 256, 0, st>>>(x4, p4, n_part, n4);
   }

@@ -31,7 +31,7 @@ def test_tiles_agree_and_match_oracle(B, G, monkeypatch):
     prm = P.make_params(B, p, G, G, MASK)
     tok_d, tgt_d = (torch.tensor(a, dtype=torch.int32, device="cuda") for a in (tok, tgt))
     got = {}
-    for tile in (None, 5, 8, 13):
+    for tile in (None, 1, 6, 7):
         if tile is not None:
             monkeypatch.setenv("WINO_GEMM_TILE", str(tile))
         model = P.WinoModel(cfg, wd, B, p + 2 * G)
@@ -67,5 +67,5 @@ def test_tiles_agree_and_match_oracle(B, G, monkeypatch):
         assert np.array_equal(ids[t][best >= 0], best[best >= 0])
         assert ((ids[t] < V // 2) | (ids[t] == MASK + V // 2)).all() and (ids[t] != MASK).all()
         # the tiles compute the same logits; only the sums' orders differ
-        assert np.array_equal(ids[t], ids[5])
-        np.testing.assert_allclose(o[:, :3], got[5][:, :3], rtol=2e-5, atol=2e-5)
+        assert np.array_equal(ids[t], ids[1])
+        np.testing.assert_allclose(o[:, :3], got[1][:, :3], rtol=2e-5, atol=2e-5)
