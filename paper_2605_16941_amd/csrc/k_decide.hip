@@ -294,21 +294,37 @@ __device__ void decide_sequence(const DecideArgs& a, int b, int* smem_i) {
 template <int U>
 __global__ __launch_bounds__(256) void decide_kernel(const DecideArgs a) {
   extern __shared__ int smem_i[];
-  decide_sequence<U>(a, blockIdx.x, smem_i);
+  const int b = blockIdx.x;
+  decide_sequence<U>(a, b, smem_i);
+  // (thread 0 wrote all of these; stores to host memory are visible to the host
+  // once it has waited for the stream)
+  if (a.host && threadIdx.x == 0) {
+    a.host[HOST_BLOCK_START * a.B + b] = a.block_start[b];
+    if (a.block_steps) a.host[HOST_BLOCK_STEPS * a.B + b] = a.block_steps[b];
+    if (a.next_verify) a.host[HOST_NEXT_VERIFY * a.B + b] = a.next_verify[b];
+    if (a.seq_steps) a.host[HOST_SEQ_STEPS * a.B + b] = a.seq_steps[b];
+    if (a.n_masked) a.host[HOST_N_MASKED * a.B + b] = a.n_masked[b];
+  }
 }
 
 // State before the first step of a call.  With advance (decode mode) a
 // sequence whose Y_cur holds no mask first moves to the first later block that
 // holds one, or to G, and its block step count restarts (a resumed or
 // pre-filled state).  Then next_verify[b] = the sequence is active and its
-// Y_cur holds both a mask and a non-mask token.  One wave per sequence.
+// Y_cur holds both a mask and a non-mask token.  The step counters given as
+// zero_* start at 0, and the state goes to the host as after a decision.  One
+// wave per sequence.
 __global__ __launch_bounds__(64) void probe_verify_kernel(const StepGeom g,
                                                           const int32_t* __restrict__ tokens,
                                                           int32_t* __restrict__ next_verify,
                                                           int32_t* block_start, int32_t* block_steps,
-                                                          int advance, int32_t* n_masked) {
+                                                          int advance, int32_t* n_masked,
+                                                          int32_t* zero_block, int32_t* zero_seq,
+                                                          int32_t* host) {
   const int b = blockIdx.x, lane = threadIdx.x;
   int bs = g.block_start[b];
+  if (lane == 0 && zero_block) zero_block[b] = 0;
+  if (lane == 0 && zero_seq) zero_seq[b] = 0;
   const int32_t* resp = tokens + (size_t)b * g.S + g.P;
   if (advance && bs >= 0 && bs < g.G) {
     int first = g.G;
@@ -335,8 +351,15 @@ __global__ __launch_bounds__(64) void probe_verify_kernel(const StepGeom g,
   nmask = (int)wave_sum((float)nmask);
   nkeep = (int)wave_sum((float)nkeep);
   if (lane == 0) {
-    next_verify[b] = nmask > 0 && nkeep > 0;
+    const int nv = nmask > 0 && nkeep > 0;
+    next_verify[b] = nv;
     if (n_masked) n_masked[b] = nmask;
+    if (host) {
+      host[HOST_BLOCK_START * g.B + b] = bs;
+      host[HOST_NEXT_VERIFY * g.B + b] = nv;
+      host[HOST_SEQ_STEPS * g.B + b] = 0;
+      host[HOST_N_MASKED * g.B + b] = nmask;
+    }
   }
 }
 
@@ -501,9 +524,9 @@ hipError_t launch_loss_merge(const LmStatsOut& lm, int R, void* out, hipStream_t
 
 hipError_t launch_probe_verify(const StepGeom& g, const int32_t* tokens, int32_t* next_verify,
                                hipStream_t st, int32_t* block_start, int32_t* block_steps,
-                               int32_t* n_masked) {
+                               int32_t* n_masked, int32_t* zero_block, int32_t* zero_seq, int32_t* host) {
   probe_verify_kernel<<<g.B, 64, 0, st>>>(g, tokens, next_verify, block_start, block_steps,
-                                          block_start != nullptr, n_masked);
+                                          block_start != nullptr, n_masked, zero_block, zero_seq, host);
   return hipGetLastError();
 }
 

@@ -159,6 +159,11 @@ hipError_t launch_attention(const StepGeom& g, const uint16_t* q, const uint16_t
 constexpr int WINO_KEEP_FLAG = 0, WINO_DRAFT_FLAG = 1, WINO_REMASK_FLAG = 2,
               WINO_FORCED_FLAG = 3, WINO_CAPFILL_FLAG = 4;
 
+// Per-sequence state a decode loop reads after each step, mirrored into pinned
+// host memory by the kernels that change it (five arrays of B ints): a loop then
+// waits for the stream and reads, where three copies per step took 4 us each.
+enum HostState { HOST_BLOCK_START = 0, HOST_BLOCK_STEPS, HOST_NEXT_VERIFY, HOST_SEQ_STEPS, HOST_N_MASKED, HOST_FIELDS };
+
 struct DecideArgs {
   // partial softmax statistics [R, n_part] (R = B*Lb rows, row b*Lb + l)
   const float* pm; const float* ps; const float* pb; const int32_t* pi; const float* pt;
@@ -185,6 +190,7 @@ struct DecideArgs {
   // [B] or null: 1 if the sequence's next step may verify (it is active and
   // its next Y_cur holds both a mask and a drafted token), else 0
   int32_t* next_verify;
+  int32_t* host;  // HostState arrays, or null
 };
 hipError_t launch_decide(const DecideArgs& a, hipStream_t st);
 // WINO+ per-row quantities (Sec. 5.3) from LM-head partials of R rows (pz
@@ -196,9 +202,13 @@ hipError_t launch_loss_merge(const LmStatsOut& lm, int R, void* out, hipStream_t
 // sequence).  With block_start (the same array as g.block_start, writable), a
 // sequence whose Y_cur holds no mask first moves to the first later block
 // holding one (or to G) and its block_steps entry (if given) restarts at 0.
+// zero_block and zero_seq (if given): step counters [B] set to 0.  host: HostState
+// arrays (all but the block steps), or null.
 hipError_t launch_probe_verify(const StepGeom& g, const int32_t* tokens, int32_t* next_verify,
                                hipStream_t st, int32_t* block_start = nullptr,
-                               int32_t* block_steps = nullptr, int32_t* n_masked = nullptr);
+                               int32_t* block_steps = nullptr, int32_t* n_masked = nullptr,
+                               int32_t* zero_block = nullptr, int32_t* zero_seq = nullptr,
+                               int32_t* host = nullptr);
 
 // Standalone epilogue statistics: for each (b, l) pick the current row
 // (masked) or the shadow row (unmasked) of bf16 logits [B, 2Lb, V], and write

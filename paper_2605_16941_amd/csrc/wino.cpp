@@ -99,7 +99,8 @@ struct wino_ctx {
   uint16_t* wcopy = nullptr;    // fp16 copies of the GEMM and LM-head weights (f16)
   Layout L{};
   char* ws = nullptr;
-  int32_t* h_pinned = nullptr;  // 4 * max_batch ints (block starts, step counts, next_verify)
+  int32_t* h_pinned = nullptr;  // HOST_FIELDS * max_batch ints of pinned memory the kernels write
+  int32_t* d_pinned = nullptr;  // its device address
   std::string err;
   // profiling
   uint32_t prof_mask = 0;
@@ -344,7 +345,7 @@ wino_status run_forward(wino_ctx* c, const StepGeom& g, const int32_t* tokens, i
 wino_status step_impl(wino_ctx* c, const wino_params* p, int32_t* tokens, int32_t* block_start,
                       int32_t* block_steps, uint8_t* flags, int32_t* n_masked, void* stats,
                       int advance, int32_t* seq_steps, bool shadow, hipStream_t st,
-                      int32_t* final_step = nullptr) {
+                      int32_t* final_step = nullptr, int32_t* host = nullptr) {
   const wino_model_config& m = c->cfg;
   shadow = shadow && p->tokens_per_step == 0;  // the baselines never verify
   const StepGeom g = make_geom(c, p, block_start, shadow);
@@ -391,6 +392,7 @@ wino_status step_impl(wino_ctx* c, const wino_params* p, int32_t* tokens, int32_
   da.topm = p->tokens_per_step;
   da.final_step = final_step;
   da.next_verify = c->next_verify();
+  da.host = host;
   {
     Bracket br(c, K_DECIDE, st);
     HIP_TRY(c, launch_decide(da, st));
@@ -545,8 +547,11 @@ wino_status wino_create(const wino_model_config* cfg, const wino_weights* w, int
   if (e != hipSuccess) return create_fail(c, WINO_ERR_HIP, "hipGetDevice", e);
   e = hipMalloc(&c->ws, c->L.total);
   if (e != hipSuccess) { c->ws = nullptr; return create_fail(c, WINO_ERR_NO_MEMORY, "hipMalloc (workspace)", e); }
-  e = hipHostMalloc(reinterpret_cast<void**>(&c->h_pinned), sizeof(int32_t) * 4 * max_batch);
+  e = hipHostMalloc(reinterpret_cast<void**>(&c->h_pinned), sizeof(int32_t) * HOST_FIELDS * max_batch,
+                    hipHostMallocMapped | hipHostMallocCoherent);
+  if (e == hipSuccess) e = hipHostGetDevicePointer(reinterpret_cast<void**>(&c->d_pinned), c->h_pinned, 0);
   if (e != hipSuccess) {
+    if (!c->d_pinned && c->h_pinned) hipHostFree(c->h_pinned);
     c->h_pinned = nullptr;
     return create_fail(c, WINO_ERR_NO_MEMORY, "hipHostMalloc", e);
   }
@@ -664,31 +669,24 @@ wino_status wino_decode_block(wino_ctx* c, const wino_params* p, int32_t* d_toke
   hipStream_t st = static_cast<hipStream_t>(stream);
   const int B = p->batch;
   const int cap = block_cap(p);
-  HIP_TRY(c, hipMemsetAsync(c->block_steps(), 0, sizeof(int32_t) * 2 * c->max_batch, st));
-  int32_t* h_nv = c->h_pinned + 2 * B;  // next_verify per sequence
+  const int32_t *h_nm = c->h_pinned + HOST_N_MASKED * B, *h_nv = c->h_pinned + HOST_NEXT_VERIFY * B;
   HIP_TRY(c, launch_probe_verify(make_geom(c, p, d_block_start), d_tokens, c->next_verify(), st,
-                                 nullptr, nullptr, c->n_masked()));
-  HIP_TRY(c, hipMemcpyAsync(h_nv, c->next_verify(), sizeof(int32_t) * B, hipMemcpyDeviceToHost, st));
-  HIP_TRY(c, hipMemcpyAsync(c->h_pinned, c->n_masked(), sizeof(int32_t) * B, hipMemcpyDeviceToHost, st));
+                                 nullptr, nullptr, c->n_masked(), c->block_steps(), c->seq_steps(), c->d_pinned));
   HIP_TRY(c, hipStreamSynchronize(st));
   // no current block holds a mask: nothing to decode, no forward
   bool any_mask = false;
-  for (int b = 0; b < B; ++b) any_mask |= c->h_pinned[b] > 0;
+  for (int b = 0; b < B; ++b) any_mask |= h_nm[b] > 0;
   for (int it = 0; any_mask; ++it) {
     s = step_impl(c, p, d_tokens, const_cast<int32_t*>(d_block_start), c->block_steps(), nullptr,
-                  c->n_masked(), nullptr, 0, c->seq_steps(), need_shadow(p, h_nv), st, d_final_step);
+                  c->n_masked(), nullptr, 0, c->seq_steps(), need_shadow(p, h_nv), st, d_final_step, c->d_pinned);
     if (s != WINO_OK) return s;
-    HIP_TRY(c, hipMemcpyAsync(c->h_pinned, c->n_masked(), sizeof(int32_t) * B, hipMemcpyDeviceToHost, st));
-    HIP_TRY(c, hipMemcpyAsync(h_nv, c->next_verify(), sizeof(int32_t) * B, hipMemcpyDeviceToHost, st));
     HIP_TRY(c, hipStreamSynchronize(st));
     bool any = false;
-    for (int b = 0; b < B; ++b) any |= c->h_pinned[b] > 0;
+    for (int b = 0; b < B; ++b) any |= h_nm[b] > 0;
     if (!any) break;
     if (it + 1 >= cap) { c->err = "block did not finish within its step cap"; return WINO_ERR_STEP_CAP; }
   }
-  if (h_steps) {
-    HIP_TRY(c, hipMemcpy(h_steps, c->seq_steps(), sizeof(int32_t) * B, hipMemcpyDeviceToHost));
-  }
+  if (h_steps) std::copy_n(c->h_pinned + HOST_SEQ_STEPS * B, B, h_steps);
   return WINO_OK;
 }
 
@@ -706,20 +704,17 @@ wino_status wino_decode(wino_ctx* c, const wino_params* p, int32_t* d_tokens, in
   const long budget = (long)(p->gen_len / p->block_len) * cap;
   // block steps: the caller's (a resumed state) or zeros
   int32_t* bsteps = d_block_steps ? d_block_steps : c->block_steps();
-  if (!d_block_steps)
-    HIP_TRY(c, hipMemsetAsync(c->block_steps(), 0, sizeof(int32_t) * c->max_batch, st));
-  HIP_TRY(c, hipMemsetAsync(c->seq_steps(), 0, sizeof(int32_t) * c->max_batch, st));
   int forwards = 0;
-  int32_t* h_nv = c->h_pinned + 2 * B;  // next_verify per sequence
+  const int32_t *h_bs = c->h_pinned + HOST_BLOCK_START * B, *h_steps = c->h_pinned + HOST_BLOCK_STEPS * B,
+                *h_nv = c->h_pinned + HOST_NEXT_VERIFY * B;
   // blocks holding no mask at the start (a resumed or pre-filled state) are skipped
   HIP_TRY(c, launch_probe_verify(make_geom(c, p, d_block_start), d_tokens, c->next_verify(), st,
-                                 d_block_start, bsteps));
-  HIP_TRY(c, hipMemcpyAsync(h_nv, c->next_verify(), sizeof(int32_t) * B, hipMemcpyDeviceToHost, st));
-  HIP_TRY(c, hipMemcpyAsync(c->h_pinned, d_block_start, sizeof(int32_t) * B, hipMemcpyDeviceToHost, st));
+                                 d_block_start, bsteps, nullptr, d_block_steps ? nullptr : c->block_steps(),
+                                 c->seq_steps(), c->d_pinned));
   HIP_TRY(c, hipStreamSynchronize(st));
   for (;;) {
     bool all_done = true;
-    for (int b = 0; b < B; ++b) all_done &= c->h_pinned[b] >= p->gen_len;
+    for (int b = 0; b < B; ++b) all_done &= h_bs[b] >= p->gen_len;
     if (all_done) break;
     if (max_forwards > 0 && forwards >= max_forwards) break;  // a resumable checkpoint
     if (forwards >= budget) {
@@ -727,22 +722,18 @@ wino_status wino_decode(wino_ctx* c, const wino_params* p, int32_t* d_tokens, in
       return WINO_ERR_STEP_CAP;
     }
     s = step_impl(c, p, d_tokens, d_block_start, bsteps, nullptr, c->n_masked(), nullptr, 1,
-                  c->seq_steps(), need_shadow(p, h_nv), st, d_final_step);
+                  c->seq_steps(), need_shadow(p, h_nv), st, d_final_step, c->d_pinned);
     if (s != WINO_OK) return s;
     ++forwards;
-    HIP_TRY(c, hipMemcpyAsync(c->h_pinned, d_block_start, sizeof(int32_t) * B, hipMemcpyDeviceToHost, st));
-    HIP_TRY(c, hipMemcpyAsync(c->h_pinned + B, bsteps, sizeof(int32_t) * B, hipMemcpyDeviceToHost, st));
-    HIP_TRY(c, hipMemcpyAsync(h_nv, c->next_verify(), sizeof(int32_t) * B, hipMemcpyDeviceToHost, st));
     HIP_TRY(c, hipStreamSynchronize(st));
     if ((p->flags & WINO_FLAG_NO_CAP_FILL) && p->tokens_per_step == 0)
       for (int b = 0; b < B; ++b)
-        if (c->h_pinned[b] < p->gen_len && c->h_pinned[B + b] >= cap) {
+        if (h_bs[b] < p->gen_len && h_steps[b] >= cap) {
           c->err = "block did not finish within its step cap";
           return WINO_ERR_STEP_CAP;
         }
   }
-  if (h_steps_per_seq)
-    HIP_TRY(c, hipMemcpy(h_steps_per_seq, c->seq_steps(), sizeof(int32_t) * B, hipMemcpyDeviceToHost));
+  if (h_steps_per_seq) std::copy_n(c->h_pinned + HOST_SEQ_STEPS * B, B, h_steps_per_seq);
   if (h_forward_passes) *h_forward_passes = forwards;
   return WINO_OK;
 }
