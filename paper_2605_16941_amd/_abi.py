@@ -119,14 +119,23 @@ EXPORTED = tuple(_protos)
 
 
 # ------------------------------------------------------------------ helpers
+# The binding's own time counts where a call's kernels take a few microseconds
+# (one block's epilogue: 10 us of kernels), so nothing is imported or looked up per
+# call and the current stream is read as a raw handle (no Stream object).
+try:
+    import torch as _torch
+    _Tensor, _i32_t, _u8_t = _torch.Tensor, _torch.int32, _torch.uint8
+    _f32_t, _bf16_t = _torch.float32, _torch.bfloat16
+except ImportError:  # int pointers only
+    _torch = _Tensor = _i32_t = _u8_t = _f32_t = _bf16_t = None
+_raw_stream = getattr(_torch._C, "_cuda_getCurrentRawStream", None) if _torch else None
+
+
 def _ptr(x, dtype=None, name="tensor"):
     """Device pointer of a torch tensor (checked), an int, or None."""
-    if x is None:
-        return None
-    if isinstance(x, int):
+    if x is None or isinstance(x, int):
         return x
-    import torch
-    if not isinstance(x, torch.Tensor):
+    if _Tensor is None or not isinstance(x, _Tensor):
         raise TypeError(f"{name}: expected a torch tensor, int pointer or None")
     if not x.is_cuda:
         raise ValueError(f"{name}: must be a device tensor")
@@ -139,6 +148,8 @@ def _ptr(x, dtype=None, name="tensor"):
 
 def _stream(stream):
     if stream is None:
+        if _raw_stream is not None and _torch.cuda.is_initialized():
+            return _raw_stream(_torch._C._cuda_getDevice())
         import torch
         return torch.cuda.current_stream().cuda_stream
     if isinstance(stream, int):
@@ -181,21 +192,19 @@ def wino_destroy(ctx: int) -> None:
 
 def wino_step(ctx, p: wino_params, tokens, block_start, block_steps=None, flags=None,
               n_masked=None, stats=None, stream=None) -> None:
-    import torch
-    _check(lib.wino_step(ctx, C.byref(p), _ptr(tokens, torch.int32, "tokens"),
-                         _ptr(block_start, torch.int32, "block_start"),
-                         _ptr(block_steps, torch.int32, "block_steps"),
-                         _ptr(flags, torch.uint8, "flags"), _ptr(n_masked, torch.int32, "n_masked"),
+    _check(lib.wino_step(ctx, C.byref(p), _ptr(tokens, _i32_t, "tokens"),
+                         _ptr(block_start, _i32_t, "block_start"),
+                         _ptr(block_steps, _i32_t, "block_steps"),
+                         _ptr(flags, _u8_t, "flags"), _ptr(n_masked, _i32_t, "n_masked"),
                          _ptr(stats, None, "stats"), _stream(stream)), "wino_step", ctx)
 
 
 def wino_decode_block(ctx, p: wino_params, tokens, block_start, final_step=None, stream=None):
     """Returns the per-sequence steps.  final_step as in wino_decode."""
-    import torch
     steps = (C.c_int32 * p.batch)()
-    fs = _ptr(final_step, torch.int32, "final_step") if final_step is not None else None
-    _check(lib.wino_decode_block(ctx, C.byref(p), _ptr(tokens, torch.int32, "tokens"),
-                                 _ptr(block_start, torch.int32, "block_start"), fs, steps,
+    fs = _ptr(final_step, _i32_t, "final_step") if final_step is not None else None
+    _check(lib.wino_decode_block(ctx, C.byref(p), _ptr(tokens, _i32_t, "tokens"),
+                                 _ptr(block_start, _i32_t, "block_start"), fs, steps,
                                  _stream(stream)), "wino_decode_block", ctx)
     return list(steps)
 
@@ -207,13 +216,12 @@ def wino_decode(ctx, p: wino_params, tokens, block_start, final_step=None, strea
     block_steps: int32 [batch] device tensor (in/out) of steps already taken
     in each current block, or None; max_forwards > 0 stops early with a
     resumable state."""
-    import torch
     steps = (C.c_int32 * p.batch)()
     fw = C.c_int32(0)
-    fs = _ptr(final_step, torch.int32, "final_step") if final_step is not None else None
-    _check(lib.wino_decode(ctx, C.byref(p), _ptr(tokens, torch.int32, "tokens"),
-                           _ptr(block_start, torch.int32, "block_start"),
-                           _ptr(block_steps, torch.int32, "block_steps"), fs, int(max_forwards), steps,
+    fs = _ptr(final_step, _i32_t, "final_step") if final_step is not None else None
+    _check(lib.wino_decode(ctx, C.byref(p), _ptr(tokens, _i32_t, "tokens"),
+                           _ptr(block_start, _i32_t, "block_start"),
+                           _ptr(block_steps, _i32_t, "block_steps"), fs, int(max_forwards), steps,
                            C.byref(fw), _stream(stream)), "wino_decode", ctx)
     return list(steps), fw.value
 
@@ -222,9 +230,8 @@ def wino_row_losses(ctx, p: wino_params, tokens, targets, out, stream=None) -> N
     """WINO+ per-row quantities of training states (Sec. 5.2-5.3).  tokens int32
     [B, P+G], targets int32 [B, G], out: device buffer of B*G wino_row_loss
     (16 bytes each: entropy, nll, conf float32; argmax int32)."""
-    import torch
-    _check(lib.wino_row_losses(ctx, C.byref(p), _ptr(tokens, torch.int32, "tokens"),
-                               _ptr(targets, torch.int32, "targets"), _ptr(out, None, "out"),
+    _check(lib.wino_row_losses(ctx, C.byref(p), _ptr(tokens, _i32_t, "tokens"),
+                               _ptr(targets, _i32_t, "targets"), _ptr(out, None, "out"),
                                _stream(stream)), "wino_row_losses", ctx)
 
 
@@ -234,13 +241,12 @@ def wino_epilogue_workspace_bytes(batch: int, block_len: int, vocab: int) -> int
 
 def wino_epilogue(p: wino_params, vocab: int, logits, cur_tokens, mask_bitmap, flags=None,
                   stats=None, workspace=None, workspace_bytes=None, stream=None) -> None:
-    import torch
     if workspace_bytes is None:
         workspace_bytes = workspace.numel() * workspace.element_size()
-    _check(lib.wino_epilogue(C.byref(p), vocab, _ptr(logits, torch.bfloat16, "logits"),
-                             _ptr(cur_tokens, torch.int32, "cur_tokens"),
-                             _ptr(mask_bitmap, torch.uint8, "mask_bitmap"),
-                             _ptr(flags, torch.uint8, "flags"), _ptr(stats, None, "stats"),
+    _check(lib.wino_epilogue(C.byref(p), vocab, _ptr(logits, _bf16_t, "logits"),
+                             _ptr(cur_tokens, _i32_t, "cur_tokens"),
+                             _ptr(mask_bitmap, _u8_t, "mask_bitmap"),
+                             _ptr(flags, _u8_t, "flags"), _ptr(stats, None, "stats"),
                              _ptr(workspace, None, "workspace"), workspace_bytes,
                              _stream(stream)), "wino_epilogue")
 
@@ -251,39 +257,35 @@ EPILOGUE_NOALLOC_MAX_BYTES = 2 << 20
 def wino_epilogue_noalloc(p: wino_params, vocab: int, logits, cur_tokens, mask_bitmap, flags=None,
                           stats=None, stream=None) -> None:
     """wino_epilogue with the library's own per-GPU scratch (no workspace)."""
-    import torch
-    _check(lib.wino_epilogue_noalloc(C.byref(p), vocab, _ptr(logits, torch.bfloat16, "logits"),
-                                     _ptr(cur_tokens, torch.int32, "cur_tokens"),
-                                     _ptr(mask_bitmap, torch.uint8, "mask_bitmap"),
-                                     _ptr(flags, torch.uint8, "flags"), _ptr(stats, None, "stats"),
+    _check(lib.wino_epilogue_noalloc(C.byref(p), vocab, _ptr(logits, _bf16_t, "logits"),
+                                     _ptr(cur_tokens, _i32_t, "cur_tokens"),
+                                     _ptr(mask_bitmap, _u8_t, "mask_bitmap"),
+                                     _ptr(flags, _u8_t, "flags"), _ptr(stats, None, "stats"),
                                      _stream(stream)), "wino_epilogue_noalloc")
 
 
 def wino_debug_logits(ctx, p: wino_params, tokens, block_start, logits, stream=None) -> None:
-    import torch
-    _check(lib.wino_debug_logits(ctx, C.byref(p), _ptr(tokens, torch.int32, "tokens"),
-                                 _ptr(block_start, torch.int32, "block_start"),
-                                 _ptr(logits, torch.float32, "logits"), _stream(stream)),
+    _check(lib.wino_debug_logits(ctx, C.byref(p), _ptr(tokens, _i32_t, "tokens"),
+                                 _ptr(block_start, _i32_t, "block_start"),
+                                 _ptr(logits, _f32_t, "logits"), _stream(stream)),
            "wino_debug_logits", ctx)
 
 
 def wino_debug_forward(ctx, p: wino_params, tokens, block_start, n_sublayers, out, stream=None) -> None:
-    import torch
-    _check(lib.wino_debug_forward(ctx, C.byref(p), _ptr(tokens, torch.int32, "tokens"),
-                                  _ptr(block_start, torch.int32, "block_start"), n_sublayers,
-                                  _ptr(out, torch.float32, "out"), _stream(stream)),
+    _check(lib.wino_debug_forward(ctx, C.byref(p), _ptr(tokens, _i32_t, "tokens"),
+                                  _ptr(block_start, _i32_t, "block_start"), n_sublayers,
+                                  _ptr(out, _f32_t, "out"), _stream(stream)),
            "wino_debug_forward", ctx)
 
 
 def wino_debug_gemm(A, W, out, stream=None) -> None:
     """out = A W^T (fp32) with the backbone GEMM kernel; A [M,K], W [N,K] bf16."""
-    import torch
     M, K = A.shape
     N = W.shape[0]
     if W.shape[1] != K or tuple(out.shape) != (M, N):
         raise ValueError("wino_debug_gemm: shape mismatch")
-    _check(lib.wino_debug_gemm(_ptr(A, torch.bfloat16, "A"), _ptr(W, torch.bfloat16, "W"), M, N, K,
-                               _ptr(out, torch.float32, "out"), _stream(stream)), "wino_debug_gemm")
+    _check(lib.wino_debug_gemm(_ptr(A, _bf16_t, "A"), _ptr(W, _bf16_t, "W"), M, N, K,
+                               _ptr(out, _f32_t, "out"), _stream(stream)), "wino_debug_gemm")
 
 
 def wino_profile(ctx, class_mask: int) -> None:
