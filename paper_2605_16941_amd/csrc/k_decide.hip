@@ -307,6 +307,31 @@ __global__ __launch_bounds__(256) void decide_kernel(const DecideArgs a) {
   }
 }
 
+// Partials of a row merged into one, a wave per row, eight loads in flight per
+// lane: the R rows' partials spread over the chip instead of one workgroup per
+// sequence reading all of its rows' (20 bytes each).
+__global__ __launch_bounds__(256) void merge_rows_kernel(const DecideArgs a, int R, float* __restrict__ out) {
+  const int lane = threadIdx.x & 63, r = blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (r >= R) return;
+  constexpr int U = 8;
+  Part p = {kNegBig, 0.f, kNegBig, kNegBig, INT_MAX};
+  for (int j0 = lane; j0 < a.n_part; j0 += 64 * U) {
+    Part q[U];
+    load_parts<U>(a, r, j0, 64, q);
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (j0 + u * 64 < a.n_part) merge(p, q[u]);
+  }
+  p = group_merge(p, 64);
+  if (lane == 0) {
+    out[r] = p.m;
+    out[(size_t)R + r] = p.s;
+    out[(size_t)2 * R + r] = p.b;
+    out[(size_t)3 * R + r] = p.t;
+    out[(size_t)4 * R + r] = __int_as_float(p.i);
+  }
+}
+
 // State before the first step of a call.  With advance (decode mode) a
 // sequence whose Y_cur holds no mask first moves to the first later block that
 // holds one, or to G, and its block step count restarts (a resumed or
@@ -530,7 +555,22 @@ hipError_t launch_probe_verify(const StepGeom& g, const int32_t* tokens, int32_t
   return hipGetLastError();
 }
 
-hipError_t launch_decide(const DecideArgs& a, hipStream_t st) {
+// Above this many partials per sequence the rows are merged first: the one
+// workgroup's reads take about 1.2 us per thousand, the extra launch about 5 us (24
+// rows x 125 partials: 8.7 us in one launch, 11.2 in two; 32 x 494: 23 and 10).
+constexpr int kPreMergeParts = 6000;
+
+hipError_t launch_decide(const DecideArgs& in, hipStream_t st) {
+  DecideArgs a = in;
+  if (a.merged && (long)a.Lb * a.n_part > kPreMergeParts) {
+    const int R = a.B * a.Lb;
+    merge_rows_kernel<<<(R + 3) / 4, 256, 0, st>>>(a, R, a.merged);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    a.pm = a.merged; a.ps = a.pm + R; a.pb = a.ps + R; a.pt = a.pb + R;
+    a.pi = reinterpret_cast<const int32_t*>(a.pt + R);
+    a.n_part = 1;
+  }
   const size_t shm = (size_t)a.Lb * 16;
   // U = 2 covers up to 2*gs partials per position in one batch (the
   // standalone epilogue); the LM head's many vocabulary tiles take batches of 8

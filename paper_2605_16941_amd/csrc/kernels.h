@@ -191,6 +191,7 @@ struct DecideArgs {
   // its next Y_cur holds both a mask and a drafted token), else 0
   int32_t* next_verify;
   int32_t* host;  // HostState arrays, or null
+  float* merged;  // room for 5 values per row: many partials may be merged first; or null
 };
 hipError_t launch_decide(const DecideArgs& a, hipStream_t st);
 // WINO+ per-row quantities (Sec. 5.3) from LM-head partials of R rows (pz

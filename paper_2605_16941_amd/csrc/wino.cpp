@@ -393,6 +393,8 @@ wino_status step_impl(wino_ctx* c, const wino_params* p, int32_t* tokens, int32_
   da.final_step = final_step;
   da.next_verify = c->next_verify();
   da.host = host;
+  // (the entropy partials' buffer, unused in a step, holds max_part floats a row)
+  da.merged = c->L.max_part >= 5 ? c->at<float>(c->L.pz) : nullptr;
   {
     Bracket br(c, K_DECIDE, st);
     HIP_TRY(c, launch_decide(da, st));
