@@ -48,6 +48,14 @@ __device__ __forceinline__ int swiglu_row(int vc, int F) {
   return c < half ? f : F + f;
 }
 
+// Row of W_qkv for virtual column vc when a wave owns half of a 128-wide head:
+// each 128-row head is taken as (elements 0..31, 64..95), (32..63, 96..127), so a
+// lane holds both elements of its rotate-half pairs.
+__device__ __forceinline__ int qkv_half_row(int vc) {
+  const int c = vc & 127, j = c >> 6, r = c & 63;
+  return (vc & ~127) + 32 * j + r + (r & 32);
+}
+
 template <int FM, int FN>
 __device__ __forceinline__ void epi_residual(const GemmCall& c, f32x16 (&acc)[FM][FN], int rowb,
                                              int colb, int lane) {
@@ -232,12 +240,19 @@ struct TileRows {
 // MFMA layout would scatter 2-byte writes over hd rows of the transposed
 // buffer.  16-byte chunks are XOR-swizzled by the row index, so the
 // half-waves' writes (4 rows apart) land in distinct banks.
-template <class A, int FM, int FN, bool TWO>
+// HR = 2: the wave owns half of a 128-wide head, elements 32j..32j+31 of each half
+// of it (qkv_half_row orders the W rows so), and its local element e is element
+// e + 32j (+ 32 from e = 32 on) of the head.  64-wide wave tiles then serve every
+// head size: with whole heads only, 128-wide heads had no 192-row tile and few small
+// ones (1444 x 12288 x 4096 201 -> 177 us, 1260 x 7680 x 2560 75 -> 65, 776 x 3072 x
+// 1024 23 -> 17, 130 x 1536 x 512 9.5 -> 6.6).
+template <class A, int FM, int FN, bool TWO, int HR>
 __device__ __forceinline__ void epi_qkv_rope(const GemmCall& c, f32x16 (&acc)[FM][FN], int rowb,
                                              int colb, int lane, uint16_t* ws) {
   constexpr int H2 = FN / 2;
-  constexpr int WTM = FM * 32, HD = FN * 32;
-  constexpr int QCH = HD / 8;   // 16-byte chunks per q/k row (power of two)
+  constexpr int WTM = FM * 32, HDL = FN * 32, HD = HDL * HR;
+  static_assert(HR == 1 || HDL == 64, "half heads of 128-wide ones");
+  constexpr int QCH = HDL / 8;  // 16-byte chunks per staged q/k row (power of two)
   constexpr int VCH = WTM / 8;  // 16-byte chunks per v^T row
   // v^T rows are 2*VCH slots of 8 bytes; slot s of row e sits at s ^ m(e),
   // m(e) = (e >> 1) & SMASK, so 32 consecutive rows written at one slot
@@ -246,14 +261,17 @@ __device__ __forceinline__ void epi_qkv_rope(const GemmCall& c, f32x16 (&acc)[FM
   constexpr int SL = 2 * VCH;
   constexpr int SMASK = SL % 16 == 0 ? 15 : SL % 8 == 0 ? 7 : SL % 4 == 0 ? 3 : 1;
   static_assert((QCH & (QCH - 1)) == 0 && 64 % QCH == 0, "q/k chunking");
-  static_assert((HD * VCH) % 64 == 0, "v^T chunking");
+  static_assert((HDL * VCH) % 64 == 0, "v^T chunking");
   const RopeOut& ro = c.rope;
   const StepGeom& g = c.geom;
   // wave-uniform: store bases and row offsets live in scalar registers
   rowb = __builtin_amdgcn_readfirstlane(rowb);
   colb = __builtin_amdgcn_readfirstlane(colb);
-  const int half = HD / 2;
+  const int half = HDL / 2;
   const int d = ro.H * HD;
+  const int hj = HR == 2 ? (colb / HDL) & 1 : 0;  // which half of the head
+  // element of the head that local element e is (e in steps of up to 32)
+  auto elem = [&](int e) { return HR == 2 ? e + 32 * hj + (e & 32) : e; };
   const int which = colb / d;               // 0 q, 1 k, 2 v
   const int head = (colb - which * d) / HD;
   if (rowb >= c.M) return;  // a wave wholly past the last row
@@ -270,7 +288,7 @@ __device__ __forceinline__ void epi_qkv_rope(const GemmCall& c, f32x16 (&acc)[FM
   // q = (lane & 31) / 8, c8 = bit 3 of lrc, and element e + 64 flips bit 3:
   // a per-lane base and a compile-time offset for every store.
   bool plain = false;
-  if constexpr (TWO && HD == 128) plain = which < 2 && tr.t0 + WTM <= g.S;
+  if constexpr (TWO && HDL == 128) plain = which < 2 && tr.t0 + WTM <= g.S;
   if (plain) {
     const int g4 = lane >> 5, q8 = (lane & 31) >> 3;
     const float* tb = ro.tab + ((size_t)(t0u + 4 * g4) * 32 + (lane & 31)) * 4;
@@ -312,10 +330,10 @@ __device__ __forceinline__ void epi_qkv_rope(const GemmCall& c, f32x16 (&acc)[FM
           if constexpr (TWO) pos = (b == tr.b0 ? cs0 : cs1) + (t - g.S);
           else pos = cur_start(g, min(b, g.B - 1)) + (t - g.S);
         }
-        uint16_t* wr = ws + lr * HD;
+        uint16_t* wr = ws + lr * HDL;
         const int sw = lr & (QCH - 1);
         float cst[2 * H2];  // (cos, sin) of elements fn*32 + (lane & 31)
-        const float* tp = ro.tab + ((size_t)pos * 32 + (lane & 31)) * (2 * H2);
+        const float* tp = ro.tab + ((size_t)pos * 32 + (lane & 31)) * (2 * H2 * HR) + 2 * hj;
         if constexpr (H2 == 2) {
           const float4 t4 = *reinterpret_cast<const float4*>(tp);
           cst[0] = t4.x; cst[1] = t4.y; cst[2] = t4.z; cst[3] = t4.w;
@@ -360,11 +378,11 @@ __device__ __forceinline__ void epi_qkv_rope(const GemmCall& c, f32x16 (&acc)[FM
       const size_t bh = (size_t)b0u * ro.H + head;
       uint16_t* dst = uniform_ptr(base + (bh * g.Tp + t0u) * HD);
       const int lrl = lane / QCH, ch = lane & (QCH - 1);
-      uint16_t* dl = dst + lrl * HD + ch * 8;
+      uint16_t* dl = dst + lrl * HD + elem(ch * 8);
 #pragma unroll
       for (int it = 0; it < WTM / RPI; ++it) {
         const int lr = it * RPI + lrl;
-        const uint4 v = *reinterpret_cast<const uint4*>(ws + lr * HD + ((ch ^ (lr & (QCH - 1))) << 3));
+        const uint4 v = *reinterpret_cast<const uint4*>(ws + lr * HDL + ((ch ^ (lr & (QCH - 1))) << 3));
         *reinterpret_cast<uint4*>(dl + it * RPI * HD) = v;
       }
     } else {
@@ -375,8 +393,8 @@ __device__ __forceinline__ void epi_qkv_rope(const GemmCall& c, f32x16 (&acc)[FM
       int b, t;
       tr.at(lr, b, t);
       const size_t bh = (size_t)b * ro.H + head;
-      const uint4 v = *reinterpret_cast<const uint4*>(ws + lr * HD + ((ch ^ (lr & (QCH - 1))) << 3));
-      *reinterpret_cast<uint4*>(base + (bh * g.Tp + t) * HD + ch * 8) = v;
+      const uint4 v = *reinterpret_cast<const uint4*>(ws + lr * HDL + ((ch ^ (lr & (QCH - 1))) << 3));
+      *reinterpret_cast<uint4*>(base + (bh * g.Tp + t) * HD + elem(ch * 8)) = v;
     }
     }
   } else {
@@ -405,7 +423,7 @@ __device__ __forceinline__ void epi_qkv_rope(const GemmCall& c, f32x16 (&acc)[FM
       const size_t bh = (size_t)b0u * ro.H + head;
       uint16_t* dst = uniform_ptr(ro.vt + bh * HD * g.Tp + t0u);
 #pragma unroll
-      for (int it = 0; it < HD * VCH / 64; ++it) {
+      for (int it = 0; it < HDL * VCH / 64; ++it) {
         int e, ch;
         if constexpr ((VCH & (VCH - 1)) == 0) {
           e = it * (64 / VCH) + lane / VCH;  // (a lane part and a constant part)
@@ -417,12 +435,12 @@ __device__ __forceinline__ void epi_qkv_rope(const GemmCall& c, f32x16 (&acc)[FM
         const int m = (e >> 1) & SMASK;
         uint4 v = *reinterpret_cast<const uint4*>(ws + e * WTM + ((ch ^ (m >> 1)) << 3));
         if (m & 1) v = make_uint4(v.z, v.w, v.x, v.y);
-        *reinterpret_cast<uint4*>(dst + (size_t)e * g.Tp + ch * 8) = v;
+        *reinterpret_cast<uint4*>(dst + (size_t)elem(e) * g.Tp + ch * 8) = v;
       }
       return;
     }
 #pragma unroll
-    for (int it = 0; it < HD * VCH / 64; ++it) {
+    for (int it = 0; it < HDL * VCH / 64; ++it) {
       const int idx = it * 64 + lane;
       const int e = idx / VCH, ch = idx - (idx / VCH) * VCH;
       const int m = (e >> 1) & SMASK;
@@ -434,7 +452,7 @@ __device__ __forceinline__ void epi_qkv_rope(const GemmCall& c, f32x16 (&acc)[FM
       tr.at(ch * 8, b, t0);
       if (r0 + 7 < c.M && t0 + 7 < g.T && (t0 & 7) == 0) {
         const size_t bh = (size_t)b * ro.H + head;
-        *reinterpret_cast<uint4*>(ro.vt + (bh * HD + e) * g.Tp + t0) = v;
+        *reinterpret_cast<uint4*>(ro.vt + (bh * HD + elem(e)) * g.Tp + t0) = v;
       } else {
         // run crosses a sequence end or the last row, or T is not a multiple
         // of 8: element stores
@@ -444,7 +462,7 @@ __device__ __forceinline__ void epi_qkv_rope(const GemmCall& c, f32x16 (&acc)[FM
           const int r = r0 + j;
           if (r >= c.M) break;
           const int bj = r / g.T, tj = r - bj * g.T;
-          ro.vt[(((size_t)bj * ro.H + head) * HD + e) * g.Tp + tj] = h[j];
+          ro.vt[(((size_t)bj * ro.H + head) * HD + elem(e)) * g.Tp + tj] = h[j];
         }
       }
     }
@@ -702,7 +720,7 @@ __global__ __launch_bounds__(WM* WN * 64, (OCC * WM * WN + 3) / 4) void gemm_ker
     const int gi = wave * B_INS + i;
     const int lkc = lpos ^ lds_swz<KB>(gi * RPI + lrow);
     const int vc = n0 + gi * RPI + lrow;
-    const int wr = EPI == EPI_SWIGLU ? swiglu_row<WTN>(vc, c.F) : vc;
+    const int wr = EPI == EPI_SWIGLU ? swiglu_row<WTN>(vc, c.F) : EPI == EPI_QKV_HALF ? qkv_half_row(vc) : vc;
     bsrc[i] = c.W + (size_t)wr * c.ldw + kbase + lkc * 8;
   }
 
@@ -935,11 +953,12 @@ __global__ __launch_bounds__(WM* WN * 64, (OCC * WM * WN + 3) / 4) void gemm_ker
   }
   else if constexpr (EPI == EPI_STORE_F32 || EPI == EPI_LOGITS) epi_store<FM, FN>(c, acc, rowb, colb, lane);
   else if constexpr (EPI == EPI_SWIGLU) epi_swiglu<A, FM, FN>(c, acc, rowb, colb, lane);
-  else if constexpr (EPI == EPI_QKV_ROPE) {
+  else if constexpr (EPI == EPI_QKV_ROPE || EPI == EPI_QKV_HALF) {
+    constexpr int HR = EPI == EPI_QKV_HALF ? 2 : 1;
     // each wave stages its WTM x WTN tile in its own LDS region
     static_assert(BM * BN <= LDS_ELEMS, "QKV staging fits the pipeline LDS");
-    if (c.geom.T >= WTM) epi_qkv_rope<A, FM, FN, true>(c, acc, rowb, colb, lane, smem + wave * (WTM * WTN));
-    else epi_qkv_rope<A, FM, FN, false>(c, acc, rowb, colb, lane, smem + wave * (WTM * WTN));
+    if (c.geom.T >= WTM) epi_qkv_rope<A, FM, FN, true, HR>(c, acc, rowb, colb, lane, smem + wave * (WTM * WTN));
+    else epi_qkv_rope<A, FM, FN, false, HR>(c, acc, rowb, colb, lane, smem + wave * (WTM * WTN));
   }
   else epi_lmstats<BM, WM, WN, FM, FN>(c, acc, m0, tn, colb, lane, wm, wn, smem);
 }
@@ -947,8 +966,9 @@ __global__ __launch_bounds__(WM* WN * 64, (OCC * WM * WN + 3) / 4) void gemm_ker
 // A tile shape: BM x BN by WM x WN waves, NST stages of KB-deep K steps (xw more
 // for W), occ workgroups per CU, and its measured times in microseconds: a unit
 // of n 64-deep K steps takes fix + n * (lat + (load + cold / r) * u), u the share
-// of the chip's 256 * occ workgroup slots in use (what the copies share) and r the
-// row tiles that read each W strip (one of them from HBM).
+// of the chip's 256 workgroup slots in use (what the copies share) or, where a CU
+// holds several, of the fullest CU's, and r the row tiles that read each W strip
+// (one of them from HBM).
 struct TileCfg {
   int BM, BN, WM, WN, KB, NST, occ, xw;
   float fix, lat, load, cold;
@@ -965,7 +985,7 @@ struct TileCfg {
 //    24576 x 4096 316 -> 272 us, 870 x 12288 x 4096 102 -> 93)
 //  - a third W stage (xw): the weights of few row tiles come from HBM, not L2
 constexpr TileCfg kTiles[] = {
-    {128, 128, 2, 2, 64, 2, 2, 0, 1.60f, 0.607f, 0.387f, 0.524f},  // 0
+    {128, 128, 2, 2, 64, 2, 2, 0, 0.57f, 0.587f, 0.401f, 0.117f},  // 0
     {32, 256, 1, 4, 64, 2, 2, 0, 0.40f, 1.037f, 0.247f, 0.000f},  // 1: LM head
     {256, 256, 4, 2, 64, 2, 1, 0, 4.58f, 1.130f, 0.415f, 0.000f},  // 2
     {256, 256, 4, 2, 64, 2, 1, 1, 5.07f, 1.041f, 0.521f, 0.000f},  // 3
@@ -976,11 +996,11 @@ constexpr TileCfg kTiles[] = {
     {64, 64, 2, 1, 64, 6, 1, 0, 1.58f, 0.245f, 0.036f, 0.095f},  // 8
     {64, 128, 2, 2, 64, 4, 1, 0, 1.48f, 0.335f, 0.049f, 0.271f},  // 9
     {32, 64, 1, 1, 64, 6, 1, 0, 1.63f, 0.169f, 0.000f, 0.287f},  // 10
-    {64, 128, 2, 2, 64, 3, 2, 0, 1.20f, 0.289f, 0.360f, 0.507f},  // 11
+    {64, 128, 2, 2, 64, 3, 2, 0, 0.90f, 0.158f, 0.526f, 0.000f},  // 11
     {128, 128, 4, 2, 64, 4, 1, 0, 2.08f, 0.397f, 0.182f, 0.139f},  // 12
-    {128, 128, 4, 1, 64, 2, 2, 0, 1.12f, 0.660f, 0.353f, 0.408f},  // 13
+    {128, 128, 4, 1, 64, 2, 2, 0, 0.50f, 0.700f, 0.312f, 0.002f},  // 13
     {192, 256, 2, 4, 64, 2, 1, 1, 4.08f, 0.870f, 0.376f, 0.000f},  // 14
-    {192, 128, 2, 2, 64, 2, 2, 0, 2.21f, 0.697f, 0.659f, 0.000f},  // 15
+    {192, 128, 2, 2, 64, 2, 2, 0, 1.50f, 0.611f, 0.760f, 0.000f},  // 15
     {256, 256, 2, 4, 64, 2, 1, 0, 6.57f, 1.116f, 0.450f, 0.000f},  // 16: QKV of 64-wide heads
     {64, 128, 2, 1, 64, 4, 1, 0, 2.55f, 0.390f, 0.024f, 0.211f},  // 17: QKV of 128-wide heads
 };
@@ -991,9 +1011,9 @@ constexpr int kNumTiles = sizeof(kTiles) / sizeof(kTiles[0]);
 // the 256-row tile takes 32-deep ones (per MFMA it moves a quarter less than a
 // plain 256x256 tile: 1024 rows x 126464 ids 1688 -> 1561 us against 128x256,
 // 836 rows 1486 -> 1532), and 32 rows two per CU serve few rows (32 x 126464
-// 168 us against 229).  RoPE needs a wave to own exactly one head, WTN == hd (64
-// or 128, checked per call); two tiles serve only it: 256x256 with 64-wide wave
-// tiles and 64x128 with 128-wide ones.
+// 168 us against 229).  RoPE needs a wave to own one head or half of a 128-wide
+// one (checked per call); two tiles serve only it: 256x256 with 64-wide wave tiles
+// and 64x128 with 128-wide ones.
 constexpr bool tile_epi(int BM, int BN, int WM, int WN, int KB, int EPI) {
   const int WTN = BN / WN;
   if ((BM == 32 && BN == 256) || (BM == 128 && BN == 256 && WM == 2))
@@ -1001,6 +1021,7 @@ constexpr bool tile_epi(int BM, int BN, int WM, int WN, int KB, int EPI) {
   if (KB == 32) return EPI == EPI_LMSTATS;
   if (EPI == EPI_LMSTATS || EPI == EPI_LOGITS) return false;
   if (EPI == EPI_QKV_ROPE) return WTN == 64 || WTN == 128;
+  if (EPI == EPI_QKV_HALF) return WTN == 64;
   return !(BM == 256 && WN == 4) && !(BM == 64 && BN == 128 && WN == 1);
 }
 
@@ -1013,7 +1034,7 @@ bool tile_ok(const GemmCall& c, const TileCfg& t) {
   // (RoPE: heads in pairs, like the 128-column rule)
   if (c.epi == EPI_QKV_ROPE) {
     const int d = c.rope.H * c.rope.hd;
-    return WTN == c.rope.hd && d % t.BN == 0 && d % (2 * c.rope.hd) == 0;
+    return (WTN == c.rope.hd || WTN * 2 == c.rope.hd) && d % t.BN == 0 && d % (2 * c.rope.hd) == 0;
   }
   if (c.epi == EPI_SWIGLU) return (c.F % (WTN / 2)) == 0;
   return true;
@@ -1027,10 +1048,11 @@ int env_int(const char* name, int dflt) {
 // Launch overhead (us), the rate weights stream from HBM (bytes/us), and what
 // split-K partials cost: bytes/us over their write in the GEMM (about 5.5) and
 // their read in the norm kernel that adds them (about 4.2), and a fixed time.
-constexpr double kLaunchUs = 2.2, kWRate = 5.6e6, kPartRate = 2.4e6, kPartUs = 2.0;
+constexpr double kLaunchUs = 2.2, kWRate = 5.6e6, kPartRate = 2.4e6, kPartUs = 1.3;
 
 double unit_us(const GemmCall& c, const TileCfg& t, double ksteps, double units) {
-  const double u = std::min(1.0, units / (256.0 * t.occ)), r = (c.M + t.BM - 1) / t.BM;
+  const double cu = t.occ > 1 ? std::ceil(units / 256.0) : units / 256.0;
+  const double u = std::min(1.0, cu / t.occ), r = (c.M + t.BM - 1) / t.BM;
   return t.fix + ksteps * (t.lat + (t.load + t.cold / r) * u);
 }
 
@@ -1142,7 +1164,7 @@ hipError_t launch_one(const GemmCall& c, hipStream_t st) {
   constexpr bool split = EPI == EPI_LMSTATS || EPI == EPI_LOGITS;
   constexpr int arows = split ? 2 * BM : BM;
   constexpr int lds = (NST * arows + (NST + XW) * BN) * KB * 2;
-  constexpr bool qkv_fits = EPI != EPI_QKV_ROPE || BM * BN * 2 <= lds;
+  constexpr bool qkv_fits = (EPI != EPI_QKV_ROPE && EPI != EPI_QKV_HALF) || BM * BN * 2 <= lds;
   if constexpr (tile_epi(BM, BN, WM, WN, KB, EPI)) {
     static_assert(lds * OCC <= 160 * 1024 && qkv_fits && (XW == 0 || !split), "tile fits LDS");
     const int nTM = (c.M + BM - 1) / BM, nTN = c.N / BN;
@@ -1161,7 +1183,10 @@ hipError_t launch_one(const GemmCall& c, hipStream_t st) {
 template <int BM, int BN, int WM, int WN, int KB, int NST, int OCC, int XW, class A>
 hipError_t launch_cfg_t(const GemmCall& c, hipStream_t st) {
   switch (c.epi) {
-    case EPI_QKV_ROPE: return launch_one<BM, BN, WM, WN, EPI_QKV_ROPE, KB, NST, OCC, XW, A>(c, st);
+    case EPI_QKV_ROPE:
+      if (c.rope.hd == 2 * (BN / WN)) return launch_one<BM, BN, WM, WN, EPI_QKV_HALF, KB, NST, OCC, XW, A>(c, st);
+      return launch_one<BM, BN, WM, WN, EPI_QKV_ROPE, KB, NST, OCC, XW, A>(c, st);
+    case EPI_QKV_HALF: break;  // (chosen above)
     case EPI_RESIDUAL: return launch_one<BM, BN, WM, WN, EPI_RESIDUAL, KB, NST, OCC, XW, A>(c, st);
     case EPI_SWIGLU: return launch_one<BM, BN, WM, WN, EPI_SWIGLU, KB, NST, OCC, XW, A>(c, st);
     case EPI_LMSTATS: return launch_one<BM, BN, WM, WN, EPI_LMSTATS, KB, NST, OCC, XW, A>(c, st);

@@ -102,6 +102,7 @@ struct LmStatsOut {   // LM head + streaming softmax statistics per (row, N-tile
 enum GemmEpi {
   EPI_QKV_ROPE = 0, EPI_RESIDUAL = 1, EPI_SWIGLU = 2, EPI_LMSTATS = 3,
   EPI_STORE_F32 = 4,  // out = A W^T (plain A)
+  EPI_QKV_HALF = 6,   // kernel instance of EPI_QKV_ROPE whose waves own half a head
   EPI_LOGITS = 5      // out = (A + A2) W^T + bias (LM-head precision, test entry point)
 };
 constexpr int kMaxResidualSplits = 8;
