@@ -57,21 +57,6 @@ __device__ __forceinline__ int qkv_half_row(int vc) {
 }
 
 template <int FM, int FN>
-__device__ __forceinline__ void epi_residual(const GemmCall& c, f32x16 (&acc)[FM][FN], int rowb,
-                                             int colb, int lane) {
-#pragma unroll
-  for (int fm = 0; fm < FM; ++fm)
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const int row = rowb + fm * 32 + mfma_row(i, lane);
-      if (row >= c.M) continue;
-      float* dst = c.outf + (size_t)row * c.ldc + colb + (lane & 31);
-#pragma unroll
-      for (int fn = 0; fn < FN; ++fn) dst[fn * 32] += acc[fm][fn][i];
-    }
-}
-
-template <int FM, int FN>
 __device__ __forceinline__ void epi_store(const GemmCall& c, f32x16 (&acc)[FM][FN], int rowb,
                                           int colb, int lane) {
   float bias[FN];
@@ -146,24 +131,6 @@ __device__ __forceinline__ void epi_residual_full(f32x16 (&acc)[FM][FN], int lan
     }
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
   }
-}
-
-// K-slice `split` of a tile above split_row0: fp32 partial
-// part[split][m - split_row0][n] (row stride N), summed into x later.
-template <int FM, int FN>
-__device__ __forceinline__ void epi_partial(const GemmCall& c, f32x16 (&acc)[FM][FN], int rowb,
-                                            int colb, int lane, int split) {
-  const size_t mt = (size_t)(c.M - c.split_row0);
-#pragma unroll
-  for (int fm = 0; fm < FM; ++fm)
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const int row = rowb + fm * 32 + mfma_row(i, lane);
-      if (row >= c.M) continue;
-      float* dst = c.part + (split * mt + (row - c.split_row0)) * c.N + colb + (lane & 31);
-#pragma unroll
-      for (int fn = 0; fn < FN; ++fn) dst[fn * 32] = acc[fm][fn][i];
-    }
 }
 
 // out = silu(gate) * up = g u / (1 + 2^(-g log2 e)), with the hardware exp2
@@ -919,36 +886,31 @@ __global__ __launch_bounds__(WM* WN * 64, (OCC * WM * WN + 3) / 4) void gemm_ker
 
   const int rowb = m0 + wm * WTM, colb = n0 + wn * WTN;
   if constexpr (EPI == EPI_RESIDUAL) {
-    // a wave's LDS region holds one 32-row fp32 block of its tile
-    constexpr bool STAGED = NW * 32 * WTN * 2 <= LDS_ELEMS;
-    if constexpr (STAGED) {
-      float* ws = reinterpret_cast<float*>(smem + wave * (32 * WTN * 2));
-      // (the batched x loads need 64 registers beside the accumulators: only
-      // for wave tiles of at most 8 MFMA blocks)
-      if (FM * FN <= 8 && !(ksplit && tail) && rowb + WTM <= c.M) {
-        const int rbu = __builtin_amdgcn_readfirstlane(rowb), cbu = __builtin_amdgcn_readfirstlane(colb);
-        if constexpr (FM * FN <= 8)
-          epi_residual_full<FM, FN>(acc, lane, ws, c.outf + (size_t)rbu * c.ldc + cbu, c.ldc);
-      } else if (!(ksplit && tail)) {
-        epi_rows16<FM, FN>(acc, lane, ws, [&](int lr, int lc, float4 v) {
-          const int row = rowb + lr;
-          if (row >= c.M) return;
-          float4* dst = reinterpret_cast<float4*>(c.outf + (size_t)row * c.ldc + colb + lc);
-          float4 x = *dst;
-          x.x += v.x; x.y += v.y; x.z += v.z; x.w += v.w;
-          *dst = x;
-        });
-      } else {
-        const size_t mt = (size_t)(c.M - c.split_row0);
-        epi_rows16<FM, FN>(acc, lane, ws, [&](int lr, int lc, float4 v) {
-          const int row = rowb + lr;
-          if (row >= c.M) return;
-          *reinterpret_cast<float4*>(c.part + (split * mt + (row - c.split_row0)) * c.N + colb + lc) = v;
-        });
-      }
+    // a wave's LDS region holds one 32-row fp32 block of its tile; the batched x
+    // loads need 64 registers beside the accumulators of at most 8 MFMA blocks
+    static_assert(NW * 32 * WTN * 2 <= LDS_ELEMS && FM * FN <= 8, "residual staging");
+    float* ws = reinterpret_cast<float*>(smem + wave * (32 * WTN * 2));
+    if (!(ksplit && tail) && rowb + WTM <= c.M) {
+      const int rbu = __builtin_amdgcn_readfirstlane(rowb), cbu = __builtin_amdgcn_readfirstlane(colb);
+      epi_residual_full<FM, FN>(acc, lane, ws, c.outf + (size_t)rbu * c.ldc + cbu, c.ldc);
+    } else if (!(ksplit && tail)) {
+      epi_rows16<FM, FN>(acc, lane, ws, [&](int lr, int lc, float4 v) {
+        const int row = rowb + lr;
+        if (row >= c.M) return;
+        float4* dst = reinterpret_cast<float4*>(c.outf + (size_t)row * c.ldc + colb + lc);
+        float4 x = *dst;
+        x.x += v.x; x.y += v.y; x.z += v.z; x.w += v.w;
+        *dst = x;
+      });
     } else {
-      if (!(ksplit && tail)) epi_residual<FM, FN>(c, acc, rowb, colb, lane);
-      else epi_partial<FM, FN>(c, acc, rowb, colb, lane, split);
+      // K-slice `split` of a tile from split_row0 on: fp32 partial
+      // part[split][m - split_row0][n] (row stride N), summed into x later
+      const size_t mt = (size_t)(c.M - c.split_row0);
+      epi_rows16<FM, FN>(acc, lane, ws, [&](int lr, int lc, float4 v) {
+        const int row = rowb + lr;
+        if (row >= c.M) return;
+        *reinterpret_cast<float4*>(c.part + (split * mt + (row - c.split_row0)) * c.N + colb + lc) = v;
+      });
     }
   }
   else if constexpr (EPI == EPI_STORE_F32 || EPI == EPI_LOGITS) epi_store<FM, FN>(c, acc, rowb, colb, lane);
