@@ -1018,9 +1018,10 @@ double unit_us(const GemmCall& c, const TileCfg& t, double ksteps, double units)
   return t.fix + ksteps * (t.lat + (t.load + t.cold / r) * u);
 }
 
-// Makespan of n_main jobs of length T followed by n_units jobs of length U,
-// each started on the slot that frees first (the hardware dispatcher's order).
-double makespan(long n_main, double T, long n_units, double U, long slots) {
+// Time of n_main units of length T followed by n_units units of length U on the 8
+// workgroup slots per `occ` of one shader engine, each started on the slot that
+// frees first.
+double engine_makespan(long n_main, double T, long n_units, double U, long slots) {
   const long R = n_main / slots, r = n_main % slots;
   const double main_end = (R + (r ? 1 : 0)) * T;
   if (n_units == 0) return main_end;
@@ -1045,8 +1046,10 @@ double makespan(long n_main, double T, long n_units, double U, long slots) {
 // Time of the partial last row tile (rem = M mod BM rows) relative to a full
 // one.  8-wave two-stage shapes skip the MFMAs of rows past M per wave (the
 // kernel's rule: a wave keeps all its 32-row blocks, only the first, or none), so
-// the busiest SIMD's remaining share sets the time, at least kPartialFloor; and a
-// tile alone on its CU still waits for its copies, kPartialLat of an idle chip's
+// the busiest SIMD's remaining share, at least kPartialFloor, sets two thirds of the
+// time; the W copies and the barriers stay (192-row tiles with 96 and 128 rows, half
+// and two thirds of the MFMAs, ran 0.66 and 0.78 of a full tile beside full ones).
+// A tile alone on its CU still waits for its copies, kPartialLat of an idle chip's
 // time.  Other shapes: a full tile.
 constexpr double kPartialFloor = 0.3, kPartialLat = 0.75;
 double partial_share(const GemmCall& c, const TileCfg& t, int rem) {
@@ -1061,7 +1064,7 @@ double partial_share(const GemmCall& c, const TileCfg& t, int rem) {
     load[w % 4] += (double)fmv / FM;
   }
   const double busiest = std::max(std::max(load[0], load[1]), std::max(load[2], load[3])) / 2.0;
-  return std::max(busiest, kPartialFloor);
+  return (1.0 + 2.0 * std::max(busiest, kPartialFloor)) / 3.0;
 }
 
 // Time of the partial last row tile's unit next to full ones of time T.
@@ -1080,7 +1083,7 @@ double tile_time(const GemmCall& c, const TileCfg& t) {
   double time = rounds * unit_us(c, t, ks, slots);
   if (rest + n_part) {
     const double T = unit_us(c, t, ks, rest + n_part);
-    time += makespan(rest, T, n_part, n_part ? partial_us(c, t, ks, T) : T, slots);
+    time += dispatch_makespan(rest, T, n_part, n_part ? partial_us(c, t, ks, T) : T, t.occ);
   }
   return std::max(kLaunchUs + time, 2.0 + 2.0 * c.N * (double)c.K / kWRate);
 }
@@ -1090,14 +1093,12 @@ double tile_time(const GemmCall& c, const TileCfg& t) {
 double residual_time(const GemmCall& c, const TileCfg& t, int tail_tm, int splits) {
   if (tail_tm == 0) return tile_time(c, t);
   const int nTM = (c.M + t.BM - 1) / t.BM, nTN = c.N / t.BN;
-  const long slots = 256L * t.occ, n_main = (long)(nTM - tail_tm) * nTN;
+  const long n_main = (long)(nTM - tail_tm) * nTN;
   const double ks = (double)c.K / BK, load = n_main + (double)tail_tm * nTN * splits;
   const double T = unit_us(c, t, ks, load), U = unit_us(c, t, ks / splits, load);
-  // (beside whole-K tiles the partial row tile's slices count as whole ones)
-  const long n_slices = (long)(tail_tm - 1) * nTN * splits, n_last = (long)nTN * splits;
-  const double last = c.M % t.BM ? std::min(U, partial_us(c, t, ks / splits, U)) : U;
-  const double span = n_main ? makespan(n_main, T, n_slices + n_last, U, slots)
-                             : makespan(n_slices, U, n_last, last, slots);
+  // (a partial row tile's slices count as whole ones: the renumbering of a split
+  // tail's units spreads them among the others)
+  const double span = dispatch_makespan(n_main, T, (long)tail_tm * nTN * splits, U, t.occ);
   const double tail_rows = c.M - (double)(nTM - tail_tm) * t.BM;
   return kLaunchUs + span + kPartUs +
          splits * tail_rows * c.N * 4.0 / kPartRate;
@@ -1165,6 +1166,23 @@ hipError_t launch_cfg(const GemmCall& c, hipStream_t st) {
 }
 
 }  // namespace
+
+// Workgroups go to the 32 shader engines (8 XCDs of 4, 8 CUs each) in turn, in
+// launch order, and wait there for a slot while another engine may have free ones.
+// Units just over a round therefore cost a whole further unit (192x256 tiles, K =
+// 2560: 240 units 55 us, 240 and 30 partial ones of 16 rows 75, where slots shared
+// by the whole chip would give 55; planned so, 1620 x 7680 x 2560 took 108 us and
+// 1800 x 3328 x 8640 168, in the tiles chosen now 82 and 129).
+double dispatch_makespan(long n_main, double T, long n_units, double U, int occ) {
+  constexpr long E = 32;
+  double end = 0;
+  // an engine's counts change at engines n_main and n_main + n_units (mod 32)
+  for (const long e : {0L, n_main % E, (n_main + n_units) % E}) {
+    const long m = (n_main - e + E - 1) / E, all = (n_main + n_units - e + E - 1) / E;
+    end = std::max(end, engine_makespan(m, T, all - m, U, 8L * occ));
+  }
+  return end;
+}
 
 void plan_residual_gemm(GemmCall& c, size_t part_elems) {
   const int f_tile = env_int("WINO_GEMM_TILE", -1);

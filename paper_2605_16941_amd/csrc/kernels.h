@@ -144,6 +144,9 @@ hipError_t launch_gemm(const GemmCall& c, hipStream_t st);
 // variables WINO_GEMM_TILE, WINO_GEMM_SPLIT and WINO_GEMM_TAIL (row tiles in
 // the split tail) force choices (tuning).
 void plan_residual_gemm(GemmCall& c, size_t part_elems);
+// Time of n_main workgroups of length T followed by n_units of length U in launch
+// order, `occ` resident per CU (the planners' model of the dispatch).
+double dispatch_makespan(long n_main, double T, long n_units, double U, int occ);
 
 // --------------------------------------------------------------- attention
 // Bidirectional attention with the WINO shadow mask (Sec. 4.2.2): query row

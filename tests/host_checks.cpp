@@ -2,6 +2,7 @@
 // and UndefinedBehaviorSanitizer on the host code (tests/test_abi_cpu.py
 // builds and runs it): every path here returns before any HIP call, so it
 // runs without a GPU.  Exits non-zero on the first failed check.
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -9,6 +10,10 @@
 #include <vector>
 
 #include "wino.h"
+
+namespace wino {
+double dispatch_makespan(long n_main, double T, long n_units, double U, int occ);  // k_gemm.hip
+}
 
 static int g_checks = 0;
 #define CHECK(cond)                                                        \
@@ -34,7 +39,34 @@ static wino_params params(int B, int P, int G, int Lb, int mask, float t1 = 0.7f
   return p;
 }
 
+// End of n_main workgroups of length T and n_units of length U dealt in turn to 32
+// shader engines of 8 CUs, each taking its own in order on the slot that frees first.
+static double simulated_makespan(long n_main, double T, long n_units, double U, int occ) {
+  std::vector<std::vector<double>> free_at(32, std::vector<double>(8 * occ, 0.0));
+  double end = 0;
+  for (long i = 0; i < n_main + n_units; ++i) {
+    std::vector<double>& f = free_at[i % 32];
+    size_t first = 0;
+    for (size_t j = 1; j < f.size(); ++j) if (f[j] < f[first]) first = j;
+    f[first] += i < n_main ? T : U;
+    end = std::max(end, f[first]);
+  }
+  return end;
+}
+
 int main() {
+  // the planners' dispatch model, around whole rounds of every occupancy
+  for (int occ = 1; occ <= 3; ++occ)
+    for (long round = 0; round <= 2; ++round)
+      for (long d : {-40L, -17L, -16L, -4L, 0L, 1L, 12L, 33L, 100L})
+        for (long units : {0L, 1L, 6L, 30L, 31L, 32L, 96L, 520L})
+          for (double U : {0.37, 0.62, 1.0}) {
+            const long n = 256L * occ * round + d;
+            if (n < 0) continue;
+            const double want = simulated_makespan(n, 1.0, units, U, occ);
+            CHECK(std::fabs(wino::dispatch_makespan(n, 1.0, units, U, occ) - want) < 1e-6);
+          }
+
   // sizes
   wino_model_config cfg = tiny_cfg();
   const size_t w1 = wino_workspace_bytes(&cfg, 1, 112), w2 = wino_workspace_bytes(&cfg, 2, 112);
