@@ -1104,23 +1104,57 @@ double residual_time(const GemmCall& c, const TileCfg& t, int tail_tm, int split
          splits * tail_rows * c.N * 4.0 / kPartRate;
 }
 
+// Plans of the calls seen last, by the values that decide them: working one out takes
+// 1-2 us of host time (4-44 with the slices of a residual call), finding it 0.1.
+struct PlanEntry {
+  int epi, M, N, K, p0, p1;  // p0, p1: heads and head size (RoPE), F (SwiGLU)
+  size_t part_elems;         // (residual)
+  int tile, splits, split_row0;  // tile: index + 1, 0 = none fits
+  bool same(const PlanEntry& o) const {
+    return epi == o.epi && M == o.M && N == o.N && K == o.K && p0 == o.p0 && p1 == o.p1 &&
+           part_elems == o.part_elems;
+  }
+};
+constexpr int kMaxPlans = 64;
+std::mutex g_plan_mu;
+PlanEntry g_plans[kMaxPlans];
+int g_n_plans = 0, g_next_plan = 0;  // (the oldest makes room)
+
+PlanEntry plan_key(const GemmCall& c, size_t part_elems) {
+  PlanEntry e{c.epi, c.M, c.N, c.K, 0, 0, part_elems, 0, 1, c.M};
+  if (c.epi == EPI_QKV_ROPE) { e.p0 = c.rope.H; e.p1 = c.rope.hd; }
+  if (c.epi == EPI_SWIGLU) e.p0 = c.F;
+  return e;
+}
+
+bool find_plan(PlanEntry& e) {
+  std::lock_guard<std::mutex> lk(g_plan_mu);
+  for (int i = 0; i < g_n_plans; ++i)
+    if (g_plans[i].same(e)) { e = g_plans[i]; return true; }
+  return false;
+}
+
+void keep_plan(const PlanEntry& e) {
+  std::lock_guard<std::mutex> lk(g_plan_mu);
+  g_plans[g_next_plan] = e;
+  g_next_plan = (g_next_plan + 1) % kMaxPlans;
+  g_n_plans = std::min(g_n_plans + 1, kMaxPlans);
+}
+
 int pick_tile(const GemmCall& c) {
   const int f = env_int("WINO_GEMM_TILE", -1);
   if (f >= 0 && f < kNumTiles && tile_ok(c, kTiles[f])) return f;
-  int best = -1;
+  PlanEntry e = plan_key(c, 0);
+  if (find_plan(e)) return e.tile - 1;
   double best_t = 0;
   for (int i = 0; i < kNumTiles; ++i) {
     if (!tile_ok(c, kTiles[i])) continue;
     const double time = tile_time(c, kTiles[i]);
-    if (best < 0 || time < best_t) { best = i; best_t = time; }
+    if (e.tile == 0 || time < best_t) { e.tile = i + 1; best_t = time; }
   }
-  return best;
+  keep_plan(e);
+  return e.tile - 1;
 }
-
-struct PlanEntry { int M, N, K; size_t part_elems; int tile, splits, split_row0; };
-std::mutex g_plan_mu;
-PlanEntry g_plans[32];
-int g_n_plans = 0;
 
 template <int BM, int BN, int WM, int WN, int EPI, int KB, int NST, int OCC, int XW, class A>
 hipError_t launch_one(const GemmCall& c, hipStream_t st) {
@@ -1188,20 +1222,15 @@ void plan_residual_gemm(GemmCall& c, size_t part_elems) {
   const int f_tile = env_int("WINO_GEMM_TILE", -1);
   const int f_split = env_int("WINO_GEMM_SPLIT", 0), f_tail = env_int("WINO_GEMM_TAIL", -1);
   const bool forced = f_tile >= 0 || f_split > 0 || f_tail >= 0;
-  if (!forced) {
-    std::lock_guard<std::mutex> lk(g_plan_mu);
-    for (int i = 0; i < g_n_plans; ++i) {
-      const PlanEntry& e = g_plans[i];
-      if (e.M == c.M && e.N == c.N && e.K == c.K && e.part_elems == part_elems) {
-        c.tile = e.tile; c.splits = e.splits; c.split_row0 = e.split_row0;
-        return;
-      }
-    }
+  c.epi = EPI_RESIDUAL;
+  PlanEntry e = plan_key(c, part_elems);
+  if (!forced && find_plan(e)) {
+    c.tile = e.tile; c.splits = e.splits; c.split_row0 = e.split_row0;
+    return;
   }
   const int nk = c.K / BK;
   int best = -1, best_s = 1, best_tail = 0;
   double best_t = 0;
-  c.epi = EPI_RESIDUAL;
   for (int i = 0; i < kNumTiles; ++i) {
     const TileCfg& t = kTiles[i];
     if (!tile_ok(c, t) || (f_tile >= 0 && i != f_tile)) continue;
@@ -1229,9 +1258,8 @@ void plan_residual_gemm(GemmCall& c, size_t part_elems) {
   c.splits = best_tail ? best_s : 1;
   c.split_row0 = best_tail ? (nTM - best_tail) * kTiles[best].BM : c.M;
   if (!forced) {
-    std::lock_guard<std::mutex> lk(g_plan_mu);
-    g_plans[g_n_plans % 32] = PlanEntry{c.M, c.N, c.K, part_elems, c.tile, c.splits, c.split_row0};
-    g_n_plans = std::min(g_n_plans + 1, 32);
+    e.tile = c.tile; e.splits = c.splits; e.split_row0 = c.split_row0;
+    keep_plan(e);
   }
 }
 

@@ -3,17 +3,15 @@
 // builds and runs it): every path here returns before any HIP call, so it
 // runs without a GPU.  Exits non-zero on the first failed check.
 #include <algorithm>
+#include <chrono>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
 #include <cstdlib>
 #include <vector>
 
+#include "kernels.h"
 #include "wino.h"
-
-namespace wino {
-double dispatch_makespan(long n_main, double T, long n_units, double U, int occ);  // k_gemm.hip
-}
 
 static int g_checks = 0;
 #define CHECK(cond)                                                        \
@@ -66,6 +64,45 @@ int main() {
             const double want = simulated_makespan(n, 1.0, units, U, occ);
             CHECK(std::fabs(wino::dispatch_makespan(n, 1.0, units, U, occ) - want) < 1e-6);
           }
+
+  // a GEMM's plan is worked out once: calls of shapes seen before (a step has about
+  // ten) take a fraction of the first ones' time and give the same plan
+  for (const bool residual : {false, true}) {
+    double first = 0, later = 1;
+    for (int K = 2560; K < 2560 + 4 * 64; K += 64) {  // (four sets of new shapes)
+      std::vector<wino::GemmCall> calls;
+      for (int m : {37, 544, 1444, 8704}) {
+        wino::GemmCall c{};
+        c.M = m; c.K = K;
+        c.epi = wino::EPI_QKV_ROPE; c.N = 3 * 2560; c.rope.H = 20; c.rope.hd = 128;
+        if (!residual) calls.push_back(c);
+        c.rope.H = 40; c.rope.hd = 64;
+        if (!residual) calls.push_back(c);
+        c.epi = wino::EPI_SWIGLU; c.N = 2 * 7616; c.F = 7616;
+        if (!residual) calls.push_back(c);
+        c.epi = wino::EPI_RESIDUAL; c.N = 2560;
+        if (residual) calls.push_back(c);
+      }
+      std::vector<int> plan, again;
+      auto pass = [&](std::vector<int>& out) {
+        out.clear();
+        const auto t0 = std::chrono::steady_clock::now();
+        for (wino::GemmCall c : calls) {
+          if (residual) wino::plan_residual_gemm(c, (size_t)8 * 1024 * c.N);
+          else c.tile = wino::gemm_tile_n(c);
+          for (int v : {c.tile, c.splits, c.split_row0}) out.push_back(v);
+        }
+        return std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
+      };
+      first += pass(plan) / 4;
+      for (int i = 0; i < 5; ++i) {
+        later = std::min(later, pass(again));
+        CHECK(plan == again);
+      }
+    }
+    std::printf("plans: first %.1f us, later %.1f us\n", first * 1e6, later * 1e6);
+    CHECK(later < first / 3);
+  }
 
   // sizes
   wino_model_config cfg = tiny_cfg();

@@ -176,8 +176,7 @@ def test_host_code_under_address_and_undefined_behaviour_sanitizers():
         assert p.returncode == 0, log
     exe = os.path.join(out, "host_checks")
     drv = os.path.join(ROOT, "tests", "host_checks.cpp")
-    r = subprocess.run([hipcc, "-x", "c++", "-O1", "-g", "-std=c++17", *SANITIZE, "-I", os.path.join(ROOT, "include"),
-                        "-c", drv, "-o", exe + ".o"], capture_output=True, text=True)
+    r = subprocess.run([hipcc, *flags, "-c", drv, "-o", exe + ".o"], capture_output=True, text=True)
     assert r.returncode == 0, r.stderr
     r = subprocess.run([hipcc, "--offload-arch=gfx950", *SANITIZE, *objs, exe + ".o", "-o", exe],
                        capture_output=True, text=True)
