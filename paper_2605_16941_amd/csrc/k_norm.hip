@@ -199,19 +199,18 @@ __global__ __launch_bounds__(NT) void select_norm_kernel(StepGeom g, int mode,
                                                          const uint16_t* __restrict__ gain,
                                                          float eps, int d, uint16_t* __restrict__ hf,
                                                          uint16_t* __restrict__ hf_lo,
-                                                         int32_t* __restrict__ target, int r0,
+                                                         int32_t* __restrict__ target,
                                                          const int32_t* __restrict__ tgt_in, int compact) {
   const int rows_per_seq = mode == 0 ? g.Lb : mode == 1 ? 2 * g.Lb : g.G;
-  const int r = blockIdx.x;
-  const int ra = r0 + r;  // row of the flattened [B, rows_per_seq] selection
-  const int b = ra / rows_per_seq, j = ra - b * rows_per_seq;
+  const int r = blockIdx.x;  // row of the flattened [B, rows_per_seq] selection
+  const int b = r / rows_per_seq, j = r - b * rows_per_seq;
   uint4 graw[CPT];
   load_gain<NT, CPT>(gain, d, graw);
   const bool lead = threadIdx.x == 0;
   int src;
   if (mode == 2) {  // response row j (WINO+ training state, no shadow block)
     src = g.P + j;
-    if (lead) target[r] = tgt_in[ra];
+    if (lead) target[r] = tgt_in[r];
   } else if (mode == 0) {
     const int c0 = cur_start(g, b);
     const int tok = tokens[(size_t)b * g.S + c0 + j];
@@ -348,16 +347,14 @@ void launch_residual_reduce(float* x, const float* part, int n_part, int part_ro
 
 void launch_select_norm(const StepGeom& g, int mode, const int32_t* tokens, const float* x,
                         const uint16_t* gain, float eps, int d, uint16_t* hf, uint16_t* hf_lo,
-                        int32_t* target, hipStream_t st, int r0, int n, const int32_t* tgt_in,
-                        bool compact) {
-  if (mode != 2) { r0 = 0; n = g.B * (mode == 0 ? g.Lb : 2 * g.Lb); }
+                        int32_t* target, hipStream_t st, const int32_t* tgt_in, bool compact) {
+  const int n = g.B * (mode == 0 ? g.Lb : mode == 1 ? 2 * g.Lb : g.G);
   if (mode != 0) compact = false;
-  if (n <= 0) return;
   const int cp = compact ? 1 : 0;
   with_row_shape(d, [&](auto nt, auto cpt) {
     constexpr int NT = decltype(nt)::value, CPT = decltype(cpt)::value;
-    if (g.f16) select_norm_kernel<ActF16, NT, CPT><<<n, NT, 0, st>>>(g, mode, tokens, x, gain, eps, d, hf, hf_lo, target, r0, tgt_in, cp);
-    else select_norm_kernel<ActBf16, NT, CPT><<<n, NT, 0, st>>>(g, mode, tokens, x, gain, eps, d, hf, hf_lo, target, r0, tgt_in, cp);
+    if (g.f16) select_norm_kernel<ActF16, NT, CPT><<<n, NT, 0, st>>>(g, mode, tokens, x, gain, eps, d, hf, hf_lo, target, tgt_in, cp);
+    else select_norm_kernel<ActBf16, NT, CPT><<<n, NT, 0, st>>>(g, mode, tokens, x, gain, eps, d, hf, hf_lo, target, tgt_in, cp);
   });
 }
 

@@ -62,15 +62,14 @@ void launch_gather_block_rows(const StepGeom& g, const float* x, int d, float* x
 // Rows the decision reads.  mode 0: one row per block position (current row
 // if the token is the mask, else the shadow row) and target = current token
 // (-1 for masked).  mode 1: all 2*Lb rows (current then shadow) per sequence.
-// mode 2: response rows r0 .. r0+n-1 of the flattened [B, G] response (row
-// P + j of sequence b for r = b*G + j), target = tgt_in[r].
+// mode 2: every row of the flattened [B, G] response (row P + j of sequence b
+// for r = b*G + j), target = tgt_in[r].
 // The normed row is written as hi = act(y) and lo = act(y - hi).
 // With compact (mode 0 only) x holds the gathered block rows of
 // launch_gather_block_rows instead of the full [B, T] stream.
 void launch_select_norm(const StepGeom& g, int mode, const int32_t* tokens, const float* x,
                         const uint16_t* gain, float eps, int d, uint16_t* hf, uint16_t* hf_lo,
-                        int32_t* target, hipStream_t st, int r0 = 0, int n = 0,
-                        const int32_t* tgt_in = nullptr, bool compact = false);
+                        int32_t* target, hipStream_t st, const int32_t* tgt_in = nullptr, bool compact = false);
 
 // --------------------------------------------------------------- GEMM
 // C = A * W^T with A [M, K] (row stride lda) and W [N, K] (row stride ldw)

@@ -355,7 +355,7 @@ wino_status step_impl(wino_ctx* c, const wino_params* p, int32_t* tokens, int32_
   {
     Bracket br(c, K_SELECT_NORM, st);
     launch_select_norm(g, 0, tokens, c->xc(), c->final_norm, m.rms_eps, m.d_model, c->hf(), c->hf_lo(),
-                       c->target(), st, 0, 0, nullptr, true);
+                       c->target(), st, nullptr, true);
     HIP_TRY(c, hipGetLastError());
     br.done(0, (double)R * m.d_model * 6);
   }
@@ -757,46 +757,40 @@ wino_status wino_row_losses(wino_ctx* c, const wino_params* p, const int32_t* d_
   lc.f16 = c->f16;
   lc.A = c->hf(); lc.A2 = c->hf_lo(); lc.lda = m.d_model; lc.W = c->lm_head; lc.ldw = m.d_model;
   lc.N = m.vocab; lc.K = m.d_model; lc.epi = EPI_LMSTATS;
-  const long total = (long)g.B * g.G;
-  // rows per pass: what the selected rows' buffers (2 * rows) and the partials
-  // (rows * max_part) hold - every row at once with 256-id tiles, so that the LM
-  // head runs one well-filled launch (4 x 256 rows in passes of 836 and 188
-  // read W twice and took 2297 us; in one pass 1561)
-  for (long r0 = 0; r0 < total;) {
-    int n = (int)std::min<long>(2 * c->L.rows, total - r0);
-    lc.M = n;
-    int bn = gemm_tile_n(lc);
-    if (bn == 0) { c->err = "no LM-head tile for this shape"; return WINO_ERR_UNSUPPORTED; }
-    int n_part = m.vocab / bn;
-    const size_t room = c->L.rows * c->L.max_part;
-    if ((size_t)n * n_part > room) {
-      lc.M = n = (int)(room / n_part);
-      bn = n > 0 ? gemm_tile_n(lc) : 0;
-      n_part = bn ? m.vocab / bn : 0;
-      if (bn == 0 || (size_t)n * n_part > room) { c->err = "LM-head partials exceed the workspace"; return WINO_ERR_UNSUPPORTED; }
-    }
-    {
-      Bracket br(c, K_SELECT_NORM, st);
-      launch_select_norm(g, 2, d_tokens, c->x(), c->final_norm, m.rms_eps, m.d_model, c->hf(), c->hf_lo(),
-                         c->target(), st, (int)r0, n, d_targets);
-      HIP_TRY(c, hipGetLastError());
-      br.done(0, (double)n * m.d_model * 8);
-    }
-    lc.lm = LmStatsOut{c->lm_bias, c->target(), p->mask_id, n_part, c->at<float>(c->L.pm),
-                       c->at<float>(c->L.ps), c->at<float>(c->L.pb), c->at<int32_t>(c->L.pi),
-                       c->at<float>(c->L.pt), c->at<float>(c->L.pz)};
-    {
-      Bracket br(c, K_LM_HEAD, st);
-      HIP_TRY(c, launch_gemm(lc, st));
-      br.done(2.0 * n * (double)m.vocab * m.d_model,
-              2.0 * ((double)n * m.d_model + (double)m.vocab * m.d_model) + 24.0 * n * n_part);
-    }
-    {
-      Bracket br(c, K_DECIDE, st);
-      HIP_TRY(c, launch_loss_merge(lc.lm, n, d_out + r0, st));
-      br.done(0, 24.0 * n * n_part + 16.0 * n);
-    }
-    r0 += n;
+  // every response row in one pass, so that the LM head runs one well-filled launch
+  // (4 x 256 rows in passes of 836 and 188 read W twice and took 2297 us; in one
+  // pass 1561).  The buffers hold them: 2 * rows > max_batch * max_seq selected rows,
+  // and rows * max_part partials, which counts 128-id tiles where every LM-head
+  // tile has 256 ids.
+  const int n = g.B * g.G;
+  lc.M = n;
+  const int bn = gemm_tile_n(lc);
+  if (bn == 0) { c->err = "no LM-head tile for this shape"; return WINO_ERR_UNSUPPORTED; }
+  const int n_part = m.vocab / bn;
+  if ((size_t)n > 2 * c->L.rows || (size_t)n * n_part > c->L.rows * c->L.max_part) {
+    c->err = "response rows exceed the workspace";
+    return WINO_ERR_UNSUPPORTED;
+  }
+  {
+    Bracket br(c, K_SELECT_NORM, st);
+    launch_select_norm(g, 2, d_tokens, c->x(), c->final_norm, m.rms_eps, m.d_model, c->hf(), c->hf_lo(),
+                       c->target(), st, d_targets);
+    HIP_TRY(c, hipGetLastError());
+    br.done(0, (double)n * m.d_model * 8);
+  }
+  lc.lm = LmStatsOut{c->lm_bias, c->target(), p->mask_id, n_part, c->at<float>(c->L.pm),
+                     c->at<float>(c->L.ps), c->at<float>(c->L.pb), c->at<int32_t>(c->L.pi),
+                     c->at<float>(c->L.pt), c->at<float>(c->L.pz)};
+  {
+    Bracket br(c, K_LM_HEAD, st);
+    HIP_TRY(c, launch_gemm(lc, st));
+    br.done(2.0 * n * (double)m.vocab * m.d_model,
+            2.0 * ((double)n * m.d_model + (double)m.vocab * m.d_model) + 24.0 * n * n_part);
+  }
+  {
+    Bracket br(c, K_DECIDE, st);
+    HIP_TRY(c, launch_loss_merge(lc.lm, n, d_out, st));
+    br.done(0, 24.0 * n * n_part + 16.0 * n);
   }
   return WINO_OK;
 }

@@ -13,8 +13,10 @@ pytestmark = pytest.mark.gpu
 V, MASK = 1024, 100
 
 
-@pytest.mark.parametrize("B,G", [(1, 1), (3, 11), (2, 64), (3, 43), (4, 64), (3, 86)])
-def test_tiles_agree_and_match_oracle(B, G, monkeypatch):
+# (the last: more response rows than the step's decision rows, B * (max_seq / 2 + 1),
+# that the workspace's partials are sized by)
+@pytest.mark.parametrize("B,G,lb", [(1, 1, 1), (3, 11, 11), (2, 64, 64), (3, 43, 43), (4, 64, 64), (3, 86, 86), (4, 64, 8)])
+def test_tiles_agree_and_match_oracle(B, G, lb, monkeypatch):
     import paper_2605_16941_amd as P
     cfg = wi.preset("tiny", n_layers=1, vocab=V, mask_id=MASK)
     w = wi.model_weights(cfg, seed=5, lm_head_std=wi.wide_lm_head_std(cfg), gain_std=0.1)
@@ -28,13 +30,13 @@ def test_tiles_agree_and_match_oracle(B, G, monkeypatch):
     rng = np.random.default_rng(B * G)
     tok = rng.integers(0, V, (B, p + G))
     tgt = rng.integers(0, V, (B, G))
-    prm = P.make_params(B, p, G, G, MASK)
+    prm = P.make_params(B, p, G, lb, MASK)
     tok_d, tgt_d = (torch.tensor(a, dtype=torch.int32, device="cuda") for a in (tok, tgt))
     got = {}
     for tile in (None, 1, 6, 7):
         if tile is not None:
             monkeypatch.setenv("WINO_GEMM_TILE", str(tile))
-        model = P.WinoModel(cfg, wd, B, p + 2 * G)
+        model = P.WinoModel(cfg, wd, B, p + G + lb)
         out = torch.full((B * G, 4), float("nan"), device="cuda")
         P.wino_row_losses(model.ctx, prm, tok_d, tgt_d, out)
         torch.cuda.synchronize()
