@@ -446,7 +446,7 @@ __device__ void chunk_stats(const uint16_t* __restrict__ logits, const int32_t* 
   }
   // bz differs from m only in the chunk holding mask_id
   const bool mask_here = mask_id >= v0 && mask_id < v1;
-  float m = valu_max<64>(mx), bz = mask_here ? valu_max<64>(nm) : m;
+  float m = valu_max(mx), bz = mask_here ? valu_max(nm) : m;
   if (lane == 0) { red[0][wave] = m; red[1][wave] = bz; }
   __syncthreads();
   m = fmaxf(fmaxf(red[0][0], red[0][1]), fmaxf(red[0][2], red[0][3]));
@@ -470,8 +470,8 @@ __device__ void chunk_stats(const uint16_t* __restrict__ logits, const int32_t* 
   for (int it = 0; it < IT; ++it)
 #pragma unroll
     for (int e = 0; e < 8; ++e) se += __builtin_amdgcn_exp2f(fmaf(elem(it, e), kLog2e, -mc));
-  se = valu_sum<64>(se);
-  bi = valu_min<64>(bi);
+  se = valu_sum(se);
+  bi = valu_min(bi);
   if (lane == 0) { red[2][wave] = se; redi[wave] = bi; }
   __syncthreads();
   if (tid == 0) {

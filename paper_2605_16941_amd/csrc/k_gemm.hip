@@ -35,7 +35,6 @@ namespace wino {
 namespace {
 
 constexpr int BK = 64;
-constexpr int LDK = BK + 8;
 
 // SwiGLU virtual columns come in blocks of WTN: the first half of a block is
 // gate rows f0..f0+WTN/2-1, the second half the up rows of the same f range,
@@ -964,7 +963,6 @@ constexpr TileCfg kTiles[] = {
     {192, 256, 2, 4, 64, 2, 1, 1, 4.08f, 0.870f, 0.376f, 0.000f},  // 14
     {192, 128, 2, 2, 64, 2, 2, 0, 1.50f, 0.611f, 0.760f, 0.000f},  // 15
     {256, 256, 2, 4, 64, 2, 1, 0, 6.57f, 1.116f, 0.450f, 0.000f},  // 16: QKV of 64-wide heads
-    {64, 128, 2, 1, 64, 4, 1, 0, 2.55f, 0.390f, 0.024f, 0.211f},  // 17: QKV of 128-wide heads
 };
 constexpr int kNumTiles = sizeof(kTiles) / sizeof(kTiles[0]);
 
@@ -974,8 +972,7 @@ constexpr int kNumTiles = sizeof(kTiles) / sizeof(kTiles[0]);
 // plain 256x256 tile: 1024 rows x 126464 ids 1688 -> 1561 us against 128x256,
 // 836 rows 1486 -> 1532), and 32 rows two per CU serve few rows (32 x 126464
 // 168 us against 229).  RoPE needs a wave to own one head or half of a 128-wide
-// one (checked per call); two tiles serve only it: 256x256 with 64-wide wave tiles
-// and 64x128 with 128-wide ones.
+// one (checked per call); the 256x256 tile with 64-wide wave tiles serves only it.
 constexpr bool tile_epi(int BM, int BN, int WM, int WN, int KB, int EPI) {
   const int WTN = BN / WN;
   if ((BM == 32 && BN == 256) || (BM == 128 && BN == 256 && WM == 2))
@@ -984,7 +981,7 @@ constexpr bool tile_epi(int BM, int BN, int WM, int WN, int KB, int EPI) {
   if (EPI == EPI_LMSTATS || EPI == EPI_LOGITS) return false;
   if (EPI == EPI_QKV_ROPE) return WTN == 64 || WTN == 128;
   if (EPI == EPI_QKV_HALF) return WTN == 64;
-  return !(BM == 256 && WN == 4) && !(BM == 64 && BN == 128 && WN == 1);
+  return !(BM == 256 && WN == 4);
 }
 
 bool tile_ok(const GemmCall& c, const TileCfg& t) {
@@ -1240,7 +1237,9 @@ void plan_residual_gemm(GemmCall& c, size_t part_elems) {
       if (f_tail >= 0 && tail != std::min(f_tail, nTM)) continue;
       const double tail_rows = c.M - (double)(nTM - tail) * t.BM;
       for (int s = tail ? 2 : 1; s <= (tail ? kMaxResidualSplits : 1); ++s) {
-        // (the split counts the norm kernels have instances for)
+        // (with five and seven slices 52 of 1048 plans changed, GEMM and norm together
+        // by 1% in the mean, 16 of them slower; not worth two more instances of each
+        // norm kernel - 544 x 4096 x 12288: 72.9 us with three, 71.8 with five)
         if (s == 5 || s == 7) continue;
         if (tail && (nk / s < 4 || s * tail_rows * c.N > (double)part_elems)) continue;
         if (tail && f_split > 0 && s != f_split) continue;
@@ -1296,7 +1295,6 @@ hipError_t launch_gemm(const GemmCall& c, hipStream_t st) {
     case 14: return launch_cfg<192, 256, 2, 4, 64, 2, 1, 1>(c, st);
     case 15: return launch_cfg<192, 128, 2, 2, 64, 2, 2>(c, st);
     case 16: return launch_cfg<256, 256, 2, 4, 64, 2, 1>(c, st);
-    case 17: return launch_cfg<64, 128, 2, 1, 64, 4, 1>(c, st);
   }
   return hipErrorInvalidValue;
 }

@@ -27,7 +27,7 @@ __device__ __forceinline__ void row_norm_store(float (&v)[CPT][8], const uint4 (
   for (int c = 0; c < CPT; ++c)
 #pragma unroll
     for (int e = 0; e < 8; ++e) ss += v[c][e] * v[c][e];
-  ss = valu_sum<64>(ss);
+  ss = valu_sum(ss);
   if constexpr (NT > 64) {
     if ((tid & 63) == 0) red[tid >> 6] = ss;
     __syncthreads();
@@ -125,70 +125,53 @@ __global__ __launch_bounds__(NT) void embed_norm_kernel(StepGeom g, const int32_
   row_norm_store<A, NT, CPT>(v, graw, eps, d, h + (size_t)m * d);
 }
 
-// RMSNorm, a workgroup per row.  NP is the number of split-K partials when
-// known at compile time (their loads are then all issued before the first
-// wait; -1: a runtime loop over them, one round trip each), added in split
-// order either way.  Rows carrying partials are the slow ones: taken first.
+// RMSNorm, a workgroup per row.  NP is the number of split-K partials, known at
+// compile time so that their loads are all issued before the first wait (a runtime
+// loop over them took one round trip each); they are added in split order.  Rows
+// carrying partials are the slow ones: taken first.
 template <class A, int NT, int CPT, int NP>
 __global__ __launch_bounds__(NT) void rmsnorm_kernel(float* __restrict__ x, const uint16_t* __restrict__ gain,
                                                      float eps, int M, int d, uint16_t* __restrict__ h,
-                                                     const float* __restrict__ part, int n_part,
-                                                     int part_row0) {
+                                                     const float* __restrict__ part, int part_row0) {
   const int r = blockIdx.x;
-  const int n_tail = n_part ? M - part_row0 : 0;
+  const int n_tail = NP ? M - part_row0 : 0;
   const int m = r < n_tail ? part_row0 + r : r - n_tail;
-  const bool has = n_part && m >= part_row0;
   float* xr = x + (size_t)m * d;
   float v[CPT][8];
   uint4 graw[CPT];
   load_row<NT, CPT>(xr, d, v);
   load_gain<NT, CPT>(gain, d, graw);
-  auto add = [&](const float (&p)[CPT][8]) {
-#pragma unroll
-    for (int c = 0; c < CPT; ++c)
-#pragma unroll
-      for (int e = 0; e < 8; ++e) v[c][e] += p[c][e];
-  };
-  if (has) {
-    const float* pr = part + (size_t)(m - part_row0) * d;
-    const size_t pstride = (size_t)(M - part_row0) * d;
-    if constexpr (NP > 0) {
+  if constexpr (NP > 0) {
+    if (m >= part_row0) {
+      const float* pr = part + (size_t)(m - part_row0) * d;
+      const size_t pstride = (size_t)(M - part_row0) * d;
       float pa[NP][CPT][8];
 #pragma unroll
       for (int s = 0; s < NP; ++s) load_row<NT, CPT>(pr + s * pstride, d, pa[s]);
 #pragma unroll
-      for (int s = 0; s < NP; ++s) add(pa[s]);
-    } else if constexpr (NP < 0) {
-      for (int s = 0; s < n_part; ++s) {
-        float pa[CPT][8];
-        load_row<NT, CPT>(pr + s * pstride, d, pa);
-        add(pa);
-      }
+      for (int s = 0; s < NP; ++s)
+#pragma unroll
+        for (int c = 0; c < CPT; ++c)
+#pragma unroll
+          for (int e = 0; e < 8; ++e) v[c][e] += pa[s][c][e];
+      store_row<NT, CPT>(xr, d, v);
     }
-    store_row<NT, CPT>(xr, d, v);
   }
   row_norm_store<A, NT, CPT>(v, graw, eps, d, h + (size_t)m * d);
 }
 
-// x += the split-K partials in split order, four elements per thread.  n4:
+// x += the NP split-K partials in split order, four elements per thread.  n4:
 // float4s of one split (rows * d / 4).
 template <int NP>
 __global__ __launch_bounds__(256) void residual_reduce_kernel(float4* __restrict__ x,
-                                                              const float4* __restrict__ part, int n_part,
-                                                              size_t n4) {
+                                                              const float4* __restrict__ part, size_t n4) {
   const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
   if (i >= n4) return;
-  float4 v = x[i];
-  auto add = [&](const float4& p) { v.x += p.x; v.y += p.y; v.z += p.z; v.w += p.w; };
-  if constexpr (NP > 0) {
-    float4 pa[NP];
+  float4 v = x[i], pa[NP];
 #pragma unroll
-    for (int s = 0; s < NP; ++s) pa[s] = part[s * n4 + i];
+  for (int s = 0; s < NP; ++s) pa[s] = part[s * n4 + i];
 #pragma unroll
-    for (int s = 0; s < NP; ++s) add(pa[s]);
-  } else {
-    for (int s = 0; s < n_part; ++s) add(part[s * n4 + i]);
-  }
+  for (int s = 0; s < NP; ++s) { v.x += pa[s].x; v.y += pa[s].y; v.z += pa[s].z; v.w += pa[s].w; }
   x[i] = v;
 }
 
@@ -300,49 +283,47 @@ void launch_embed_norm(const StepGeom& g, const int32_t* tokens, const uint16_t*
   });
 }
 
-template <class A>
-void rmsnorm_impl(float* x, const uint16_t* gain, float eps, int M, int d, uint16_t* h,
-                  const float* part, int n_part, int part_row0, hipStream_t st) {
-  if (!part) n_part = 0;
+// Runs f(split count) for the counts the residual planner uses; false for others.
+template <class F>
+bool with_splits(int n, F f) {
+  using std::integral_constant;
+  switch (n) {
+    case 2: f(integral_constant<int, 2>{}); return true;
+    case 3: f(integral_constant<int, 3>{}); return true;
+    case 4: f(integral_constant<int, 4>{}); return true;
+    case 6: f(integral_constant<int, 6>{}); return true;
+    case 8: f(integral_constant<int, 8>{}); return true;
+  }
+  return false;
+}
+
+hipError_t launch_rmsnorm(float* x, const uint16_t* gain, float eps, int M, int d, uint16_t* h,
+                          const float* part, int n_part, int part_row0, hipStream_t st, bool f16) {
+  bool ok = true;
   with_row_shape(d, [&](auto nt, auto cpt) {
     constexpr int NT = decltype(nt)::value, CPT = decltype(cpt)::value;
     auto go = [&](auto np) {
-      rmsnorm_kernel<A, NT, CPT, decltype(np)::value><<<M, NT, 0, st>>>(x, gain, eps, M, d, h, part, n_part, part_row0);
+      constexpr int NP = decltype(np)::value;
+      if (f16) rmsnorm_kernel<ActF16, NT, CPT, NP><<<M, NT, 0, st>>>(x, gain, eps, M, d, h, part, part_row0);
+      else rmsnorm_kernel<ActBf16, NT, CPT, NP><<<M, NT, 0, st>>>(x, gain, eps, M, d, h, part, part_row0);
     };
-    // the split counts the residual planner uses get their own instance
-    switch (n_part) {
-      case 0: go(std::integral_constant<int, 0>{}); break;
-      case 2: go(std::integral_constant<int, 2>{}); break;
-      case 3: go(std::integral_constant<int, 3>{}); break;
-      case 4: go(std::integral_constant<int, 4>{}); break;
-      case 6: go(std::integral_constant<int, 6>{}); break;
-      case 8: go(std::integral_constant<int, 8>{}); break;
-      default: go(std::integral_constant<int, -1>{});
-    }
+    if (!part || n_part == 0) go(std::integral_constant<int, 0>{});
+    else ok = with_splits(n_part, go);
   });
+  return ok ? hipGetLastError() : hipErrorInvalidValue;
 }
 
-void launch_rmsnorm(float* x, const uint16_t* gain, float eps, int M, int d, uint16_t* h,
-                    const float* part, int n_part, int part_row0, hipStream_t st, bool f16) {
-  if (f16) rmsnorm_impl<ActF16>(x, gain, eps, M, d, h, part, n_part, part_row0, st);
-  else rmsnorm_impl<ActBf16>(x, gain, eps, M, d, h, part, n_part, part_row0, st);
-}
-
-void launch_residual_reduce(float* x, const float* part, int n_part, int part_row0, int M, int d,
-                            hipStream_t st) {
-  if (M - part_row0 <= 0) return;
+hipError_t launch_residual_reduce(float* x, const float* part, int n_part, int part_row0, int M, int d,
+                                  hipStream_t st) {
+  if (M - part_row0 <= 0) return hipSuccess;
   const size_t n4 = (size_t)(M - part_row0) * (d / 4);
   float4* x4 = reinterpret_cast<float4*>(x + (size_t)part_row0 * d);
   const float4* p4 = reinterpret_cast<const float4*>(part);
   const unsigned grid = (unsigned)((n4 + 255) / 256);
-  switch (n_part) {
-    case 2: residual_reduce_kernel<2><<<grid, 256, 0, st>>>(x4, p4, n_part, n4); break;
-    case 3: residual_reduce_kernel<3><<<grid, 256, 0, st>>>(x4, p4, n_part, n4); break;
-    case 4: residual_reduce_kernel<4><<<grid, 256, 0, st>>>(x4, p4, n_part, n4); break;
-    case 6: residual_reduce_kernel<6><<<grid, 256, 0, st>>>(x4, p4, n_part, n4); break;
-    case 8: residual_reduce_kernel<8><<<grid, 256, 0, st>>>(x4, p4, n_part, n4); break;
-    default: residual_reduce_kernel<-1><<<grid, 256, 0, st>>>(x4, p4, n_part, n4);
-  }
+  const bool ok = with_splits(n_part, [&](auto np) {
+    residual_reduce_kernel<decltype(np)::value><<<grid, 256, 0, st>>>(x4, p4, n4);
+  });
+  return ok ? hipGetLastError() : hipErrorInvalidValue;
 }
 
 void launch_select_norm(const StepGeom& g, int mode, const int32_t* tokens, const float* x,

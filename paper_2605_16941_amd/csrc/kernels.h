@@ -45,17 +45,18 @@ void launch_embed_norm(const StepGeom& g, const int32_t* tokens, const uint16_t*
 // h[m] = rmsnorm(x[m]) * gain for m < M.  With n_part > 0 the split-K
 // partials of rows m >= part_row0, part[s][m - part_row0] (s < n_part, fp32
 // [n_part, M - part_row0, d]), are first added to x[m] in order s = 0, 1, ...
-// and x is written back.
-void launch_rmsnorm(float* x, const uint16_t* gain, float eps, int M, int d, uint16_t* h,
-                    const float* part, int n_part, int part_row0, hipStream_t st, bool f16);
+// and x is written back.  n_part: 0 or a split count of the residual planner (2, 3,
+// 4, 6, 8); hipErrorInvalidValue otherwise.
+hipError_t launch_rmsnorm(float* x, const uint16_t* gain, float eps, int M, int d, uint16_t* h,
+                          const float* part, int n_part, int part_row0, hipStream_t st, bool f16);
 // out = fp16(in) for n bf16 values (n a multiple of 8), round to nearest even;
 // *overflow is set to 1 if an output is not finite (|in| beyond fp16's range,
 // or a non-finite input), else left as it is.
 void launch_bf16_to_f16(const uint16_t* in, uint16_t* out, size_t n, int* overflow, hipStream_t st);
-// x[m] += sum_s part[s][m - part_row0] (same order as above), for
+// x[m] += sum_s part[s][m - part_row0] (same order and split counts as above), for
 // part_row0 <= m < M.
-void launch_residual_reduce(float* x, const float* part, int n_part, int part_row0, int M, int d,
-                            hipStream_t st);
+hipError_t launch_residual_reduce(float* x, const float* part, int n_part, int part_row0, int M, int d,
+                                  hipStream_t st);
 // xc[b*(Lb+Ls) + i] = x row c0+i (i < Lb) or S+i-Lb (the shadow rows): the
 // rows of the current block and the shadow block, fp32 [B*(Lb+Ls), d].
 void launch_gather_block_rows(const StepGeom& g, const float* x, int d, float* xc, hipStream_t st);

@@ -293,9 +293,8 @@ wino_status run_forward(wino_ctx* c, const StepGeom& g, const int32_t* tokens, i
     if (2 * l + 1 >= n_sub) break;
     {
       Bracket br(c, K_RMSNORM, st);
-      launch_rmsnorm(xr, c->ffn_norm[l], m.rms_eps, Mr, d, c->h(), c->part(), pend.n, pend.row0, st,
-                     c->f16);
-      HIP_TRY(c, hipGetLastError());
+      HIP_TRY(c, launch_rmsnorm(xr, c->ffn_norm[l], m.rms_eps, Mr, d, c->h(), c->part(), pend.n, pend.row0, st,
+                                c->f16));
       br.done(0, norm_bytes(Mr, d, pend));
       pend = Pending{};
     }
@@ -321,17 +320,15 @@ wino_status run_forward(wino_ctx* c, const StepGeom& g, const int32_t* tokens, i
     }
     if (l + 1 < m.n_layers && 2 * (l + 1) < n_sub) {
       Bracket br(c, K_RMSNORM, st);
-      launch_rmsnorm(x, c->attn_norm[l + 1], m.rms_eps, M, d, c->h(), c->part(), pend.n,
-                     pend.row0, st, c->f16);
-      HIP_TRY(c, hipGetLastError());
+      HIP_TRY(c, launch_rmsnorm(x, c->attn_norm[l + 1], m.rms_eps, M, d, c->h(), c->part(), pend.n,
+                                pend.row0, st, c->f16));
       br.done(0, norm_bytes(M, d, pend));
       pend = Pending{};
     }
   }
   if (pend.n) {
     Bracket br(c, K_RMSNORM, st);
-    launch_residual_reduce(xr, c->part(), pend.n, pend.row0, Mr, d, st);
-    HIP_TRY(c, hipGetLastError());
+    HIP_TRY(c, launch_residual_reduce(xr, c->part(), pend.n, pend.row0, Mr, d, st));
     const double rows = Mr - pend.row0;
     br.done(0, rows * d * 8 + 4.0 * rows * d * pend.n);
   }
