@@ -2,6 +2,9 @@
 and the comparison rules (logits tolerance, decision margin)."""
 from __future__ import annotations
 
+import os
+import re
+
 import numpy as np
 import torch
 
@@ -52,6 +55,16 @@ def forced_is_robust(conf: np.ndarray, masked: np.ndarray, m: float = MARGIN) ->
     top-2 gap exceeds the margin."""
     c = np.sort(conf[masked])
     return len(c) < 2 or (c[-1] - c[-2]) > m
+
+
+def tile_table():
+    """(BM, BN, WM, WN, KB, stages, workgroups per CU, extra W stages) of every entry of
+    the GEMM tile table, in the order that WINO_GEMM_TILE counts."""
+    path = os.path.join(os.path.dirname(os.path.abspath(__file__)), "..", "paper_2605_16941_amd", "csrc", "k_gemm.hip")
+    with open(path) as f:
+        src = f.read()
+    body = src[src.index("constexpr TileCfg kTiles[]"):src.index("constexpr int kNumTiles")]
+    return [tuple(int(v) for v in m.group(1).split(",")) for m in re.finditer(r"\{((?:\d+, ){7}\d+), [\d.]+f", body)]
 
 
 # ------------------------------------------------------------------ workloads

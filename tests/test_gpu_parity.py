@@ -18,7 +18,8 @@ import wino_inputs as wi
 from oracle import model as M
 from oracle import wino as W
 from helpers import (LOGIT_TOL, RANK_GAP, batch_tokens, decided_mask, decode_prefix_compare, forced_is_robust, fp64_provider,
-                     gpu_step, oracle_params, oracle_trajectory, rowwise_rel_err, tiny, to_cpu, to_device)
+                     gpu_step, oracle_params, oracle_trajectory, rowwise_rel_err, tile_table, tiny, to_cpu,
+                     to_device)
 
 pytestmark = pytest.mark.gpu
 
@@ -635,14 +636,14 @@ def test_step_is_deterministic(P):
 # ---------------------------------------------------------------- GEMM tiles
 @pytest.mark.parametrize("M,N,K", [(544, 512, 4096), (100, 512, 1024), (1, 256, 256)])
 def test_gemm_tiles_within_exact_product_bound(P, M, N, K, monkeypatch):
-    """Each entry of the GEMM tile table, forced through WINO_GEMM_TILE (an
-    entry that cannot serve the call falls back to the planner's choice),
-    against the float64 sum of the same bf16 products.  Products of bf16
-    values are exact in fp32, so any order of fp32 additions stays within
-    (K-1)*2^-24 * sum|a*w| of that sum.  Ragged M (544 = 2*256 + 32, 100, 1)
-    covers the partial row tiles whose waves skip rows past M.  The tiles
-    with a third W stage change only when the copies land: they reproduce
-    their two-stage twins (entries 6 and 9) bit for bit."""
+    """Each entry of the GEMM tile table, forced through WINO_GEMM_TILE (the
+    entries of the LM head and of RoPE alone cannot serve this call: it then
+    runs the planner's choice), against the float64 sum of the same bf16
+    products.  Products of bf16 values are exact in fp32, so any order of fp32
+    additions stays within (K-1)*2^-24 * sum|a*w| of that sum.  Ragged M (544 =
+    2*256 + 32, 100, 1) covers the partial row tiles whose waves skip rows past
+    M.  All entries add the products in the same order, so they agree bit for
+    bit; a third W stage changes only when the copies land."""
     gen = torch.Generator().manual_seed(M * 7 + K)
     A = torch.randn(M, K, generator=gen).bfloat16()
     Wt = (torch.randn(N, K, generator=gen) * 0.02).bfloat16()
@@ -650,7 +651,9 @@ def test_gemm_tiles_within_exact_product_bound(P, M, N, K, monkeypatch):
     bound = (K - 1) * 2.0 ** -24 * (A.double().abs() @ Wt.double().abs().T)
     Ad, Wd = A.cuda(), Wt.cuda()
     outs = {}
-    for t in range(16):
+    table = tile_table()
+    assert any(t[7] for t in table) and all(N % t[1] == 0 for t in table)
+    for t in range(len(table)):
         monkeypatch.setenv("WINO_GEMM_TILE", str(t))
         out = torch.full((M, N), float("nan"), device="cuda")
         P.wino_debug_gemm(Ad, Wd, out)
@@ -658,7 +661,7 @@ def test_gemm_tiles_within_exact_product_bound(P, M, N, K, monkeypatch):
         outs[t] = out.cpu()
         err = (outs[t].double() - ref).abs()
         assert bool((err <= bound).all()), (t, float((err / bound.clamp_min(1e-300)).max()))
-    assert torch.equal(outs[6], outs[11]) and torch.equal(outs[9], outs[12])
+        assert torch.equal(outs[t], outs[0]), t
 
 
 
