@@ -1085,24 +1085,23 @@ double tile_time(const GemmCall& c, const TileCfg& t) {
   return std::max(kLaunchUs + time, 2.0 + 2.0 * c.N * (double)c.K / kWRate);
 }
 
-// Residual GEMM whose last tail_tm row tiles are computed as `splits` K-slices
-// that write fp32 partials for the next norm kernel.
-double residual_time(const GemmCall& c, const TileCfg& t, int tail_tm, int splits) {
-  if (tail_tm == 0) return tile_time(c, t);
-  const int nTM = (c.M + t.BM - 1) / t.BM, nTN = c.N / t.BN;
-  const long n_main = (long)(nTM - tail_tm) * nTN;
-  const double ks = (double)c.K / BK, load = n_main + (double)tail_tm * nTN * splits;
-  const double T = unit_us(c, t, ks, load), U = unit_us(c, t, ks / splits, load);
+// Residual GEMM whose last tail_tm > 0 row tiles are computed as `splits` K-slices
+// that write fp32 partials for the next norm kernel; HUGE_VAL if this, and so more
+// slices too, cannot take less than `limit` (an even spread of the units over the
+// slots, which grows with the slices, already does not).
+double residual_time(const GemmCall& c, const TileCfg& t, int nTM, int nTN, int tail_tm, int splits, double limit) {
+  const long n_main = (long)(nTM - tail_tm) * nTN, n_slices = (long)tail_tm * nTN * splits;
+  const double ks = (double)c.K / BK, tail_rows = c.M - (double)(nTM - tail_tm) * t.BM;
+  const double rest = kLaunchUs + kPartUs + splits * tail_rows * c.N * (4.0 / kPartRate);
+  const double T = unit_us(c, t, ks, n_main + n_slices), U = t.fix + (T - t.fix) / splits;
+  if (rest + (n_main * T + n_slices * U) / (256 * t.occ) >= limit) return HUGE_VAL;
   // (a partial row tile's slices count as whole ones: the renumbering of a split
   // tail's units spreads them among the others)
-  const double span = dispatch_makespan(n_main, T, (long)tail_tm * nTN * splits, U, t.occ);
-  const double tail_rows = c.M - (double)(nTM - tail_tm) * t.BM;
-  return kLaunchUs + span + kPartUs +
-         splits * tail_rows * c.N * 4.0 / kPartRate;
+  return rest + dispatch_makespan(n_main, T, n_slices, U, t.occ);
 }
 
 // Plans of the calls seen last, by the values that decide them: working one out takes
-// 1-2 us of host time (4-44 with the slices of a residual call), finding it 0.1.
+// 1-2 us of host time (3-16 with the slices of a residual call), finding it 0.1.
 struct PlanEntry {
   int epi, M, N, K, p0, p1;  // p0, p1: heads and head size (RoPE), F (SwiGLU)
   size_t part_elems;         // (residual)
@@ -1227,27 +1226,33 @@ void plan_residual_gemm(GemmCall& c, size_t part_elems) {
   }
   const int nk = c.K / BK;
   int best = -1, best_s = 1, best_tail = 0;
-  double best_t = 0;
-  for (int i = 0; i < kNumTiles; ++i) {
-    const TileCfg& t = kTiles[i];
-    if (!tile_ok(c, t) || (f_tile >= 0 && i != f_tile)) continue;
-    const int nTM = (c.M + t.BM - 1) / t.BM;
-    for (int tail = 0; tail <= nTM; ++tail) {
-      if (tail > 8 && tail < nTM) continue;  // (a few trailing row tiles, or all)
-      if (f_tail >= 0 && tail != std::min(f_tail, nTM)) continue;
-      const double tail_rows = c.M - (double)(nTM - tail) * t.BM;
-      for (int s = tail ? 2 : 1; s <= (tail ? kMaxResidualSplits : 1); ++s) {
+  double best_t = HUGE_VAL;
+  auto consider = [&](int i, int tail, int splits, double time) {
+    if (time < best_t) { best = i; best_t = time; best_s = splits; best_tail = tail; }
+  };
+  // whole-K tiles and the split of every row tile first: they bound the rest
+  for (const bool some : {false, true})
+    for (int i = 0; i < kNumTiles; ++i) {
+      const TileCfg& t = kTiles[i];
+      if (!tile_ok(c, t) || (f_tile >= 0 && i != f_tile)) continue;
+      const int nTM = (c.M + t.BM - 1) / t.BM, nTN = c.N / t.BN;
+      if (!some && (f_tail < 0 || f_tail == 0)) consider(i, 0, 1, tile_time(c, t));
+      // (a few trailing row tiles, or all)
+      for (int tail = some ? 1 : nTM; tail <= (some ? std::min(8, nTM - 1) : nTM); ++tail) {
+        if (f_tail >= 0 && tail != std::min(f_tail, nTM)) continue;
+        const double tail_rows = c.M - (double)(nTM - tail) * t.BM;
         // (with five and seven slices 52 of 1048 plans changed, GEMM and norm together
         // by 1% in the mean, 16 of them slower; not worth two more instances of each
         // norm kernel - 544 x 4096 x 12288: 72.9 us with three, 71.8 with five)
-        if (s == 5 || s == 7) continue;
-        if (tail && (nk / s < 4 || s * tail_rows * c.N > (double)part_elems)) continue;
-        if (tail && f_split > 0 && s != f_split) continue;
-        const double time = residual_time(c, t, tail, s);
-        if (best < 0 || time < best_t) { best = i; best_t = time; best_s = s; best_tail = tail; }
+        for (const int s : {2, 3, 4, 6, 8}) {
+          if (nk / s < 4 || s * tail_rows * c.N > (double)part_elems) break;
+          if (f_split > 0 && s != f_split) continue;
+          const double time = residual_time(c, t, nTM, nTN, tail, s, best_t);
+          if (time == HUGE_VAL) break;
+          consider(i, tail, s, time);
+        }
       }
     }
-  }
   if (best < 0) {  // no candidate under the overrides (or at all): whole-K tiles
     c.tile = 0; c.splits = 1; c.split_row0 = c.M;
     return;

@@ -105,7 +105,6 @@ enum GemmEpi {
   EPI_QKV_HALF = 6,   // kernel instance of EPI_QKV_ROPE whose waves own half a head
   EPI_LOGITS = 5      // out = (A + A2) W^T + bias (LM-head precision, test entry point)
 };
-constexpr int kMaxResidualSplits = 8;
 
 struct GemmCall {
   int tile;  // 1 + tile shape index; 0 (zero-initialised call): chosen per call
