@@ -90,7 +90,7 @@ def test_uneven_k_slices(d, f16, split, monkeypatch):
         return out.cpu().numpy()
 
     monkeypatch.setenv("WINO_GEMM_SPLIT", str(split))
-    want = {n: run(n, 0, 0) for n in (1, 2, 3)}
+    want = {n: run(n, 0, 0) for n in (2, 3)}
     x = np.abs(want[2]).max(-1, keepdims=True)
     table = tile_table()
     # a two-, three-, four- and six-stage tile, a third W stage, three-block waves

@@ -8,6 +8,7 @@ import torch
 
 import wino_inputs as wi
 from oracle import model as M
+from helpers import tile_table
 
 pytestmark = pytest.mark.gpu
 V, MASK = 1024, 100
@@ -33,7 +34,9 @@ def test_tiles_agree_and_match_oracle(B, G, lb, monkeypatch):
     prm = P.make_params(B, p, G, lb, MASK)
     tok_d, tgt_d = (torch.tensor(a, dtype=torch.int32, device="cuda") for a in (tok, tgt))
     got = {}
-    for tile in (None, 1, 6, 7):
+    tiles = [i for i, t in enumerate(tile_table()) if t[:4] in ((32, 256, 1, 4), (128, 256, 2, 4)) or t[4] == 32]
+    assert len(tiles) == 3
+    for tile in (None, *tiles):
         if tile is not None:
             monkeypatch.setenv("WINO_GEMM_TILE", str(tile))
         model = P.WinoModel(cfg, wd, B, p + G + lb)
@@ -69,5 +72,5 @@ def test_tiles_agree_and_match_oracle(B, G, lb, monkeypatch):
         assert np.array_equal(ids[t][best >= 0], best[best >= 0])
         assert ((ids[t] < V // 2) | (ids[t] == MASK + V // 2)).all() and (ids[t] != MASK).all()
         # the tiles compute the same logits; only the sums' orders differ
-        assert np.array_equal(ids[t], ids[1])
-        np.testing.assert_allclose(o[:, :3], got[1][:, :3], rtol=2e-5, atol=2e-5)
+        assert np.array_equal(ids[t], ids[tiles[0]])
+        np.testing.assert_allclose(o[:, :3], got[tiles[0]][:, :3], rtol=2e-5, atol=2e-5)
