@@ -939,10 +939,10 @@ struct TileCfg {
 // 256-24576, K 256-12288, both types, weights from HBM), LM head tiles over 11
 // (16-1024 rows x 4096-126464 ids).  On gate/up products the model is within 4-12%
 // rms per tile where the tile is competitive (18% for the smallest), and the plans
-// are 2.4% behind the fastest measured choice on those shapes and 3.0% on 478 others
-// in the mean.  RoPE at sequence lengths that are not a multiple of 8
-// takes 15-35% longer than modelled on every tile (v^T leaves in 2-byte stores), so
-// it moves no choice much.  What each shape is for:
+// are 1.7% behind the fastest measured choice on those shapes and 2.4% on 478 others
+// in the mean.  RoPE at sequence lengths that are not a multiple of 8 takes 15-35%
+// longer than modelled on every tile (v^T leaves in 2-byte stores), so it moves no
+// choice much.  What each shape is for:
 //  - few units, bound by the latency of the copies: small tiles that keep many
 //    stages in flight (entries 8-12; 64 rows x 24576 x 4096 58 -> 45 us, 128 x
 //    17408 x 3072 62 -> 37, 32 x 256 x 704 9.5 -> 5.9)
